@@ -86,6 +86,13 @@ RouteOut route_out(const ft_route_t *r) {
                     r->hit_off, r->miss_off, r->counts};
 }
 
+// Upper bound of the evaluation groups of a call, the shared expert's included.
+int max_groups_of(const ft_moe_desc_t *d, int T) {
+    const int shared = d->shared_slot >= 0 ? 1 : 0;
+    const long mg = std::min<long>({d->n_experts, d->n_slots - shared, static_cast<long>(T) * d->top_k});
+    return static_cast<int>(mg) + shared;
+}
+
 RouteArgs route_args(const ft_moe_desc_t *d, const float *logits, const int32_t *slot_table, int T,
                      const ft_route_t *route, const WsView &wv) {
     RouteArgs a{};
@@ -101,6 +108,7 @@ RouteArgs route_args(const ft_moe_desc_t *d, const float *logits, const int32_t 
     while ((1 << nbits) < d->n_experts) ++nbits;
     a.nbits = nbits;
     a.scan_parts = 1;
+    a.skinny_rows = skinny_rows_of(T, d->act_quant);
     a.ro = route_out(route);
     a.wv = wv;
     return a;
@@ -217,11 +225,8 @@ hipError_t enqueue_experts(const ft_moe_desc_t *desc, const ft_banks_t *banks, c
     ea.n_slots = desc->n_slots;
     ea.shared = desc->shared_slot >= 0 ? 1 : 0;
     ea.act_quant = desc->act_quant;
-    const long routed_slots = desc->n_slots - ea.shared;
-    long mg = desc->n_experts;
-    if (routed_slots < mg) mg = routed_slots;
-    if (static_cast<long>(T) * desc->top_k < mg) mg = static_cast<long>(T) * desc->top_k;
-    ea.max_groups = static_cast<int>(mg) + ea.shared;
+    ea.max_groups = max_groups_of(desc, T);
+    ea.skinny_rows = skinny_rows_of(T, desc->act_quant);
     ea.ro = route_out(route);
     ea.wv = wv;
     return launch_experts(ea, s, prof);
@@ -564,6 +569,7 @@ ft_status_t ft_moe_step_hybrid(const ft_moe_desc_t *desc, const ft_banks_t *dev_
     rg.T = T;
     rg.k = desc->top_k;
     rg.shared_slot = desc->shared_slot;
+    rg.skinny_rows = skinny_rows_of(T, desc->act_quant);
     rg.hit_off = route->hit_off;
     rg.miss_off = route->miss_off;
     rg.hit_pairs = route->hit_pairs;

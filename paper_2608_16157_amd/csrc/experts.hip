@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kGemvThreads, (gemv_min_blocks<WT, EPI, MTX>())) vo
         int32_t *sk = s_route + route_wave_lds_bytes(a.E, ncnt) / 4;
         const WaveRouteSink sink{sk, sk + 1, sk + 1 + (kWave + 1), sk + 1 + 2 * (kWave + 1), sk + 1 + 3 * (kWave + 1)};
         const RouteArgs ra{a.logits, a.slot_table, a.T, a.E, a.k, a.gating, a.n_slots, a.shared_slot, a.nbits, 1,
-                           a.ro, a.wv};
+                           0, a.ro, a.wv};
         if (threadIdx.x < kWave) route_wave_body<RNPL, true>(ra, s_route, blockIdx.x == 0, sink);
         __syncthreads();
         if (g >= *sink.G) return;
@@ -615,12 +615,16 @@ static hipError_t launch_stream_path(const ExpertArgs &a, hipStream_t s, const P
         if (hipError_t e = launch_act_quant_x(a, s); e != hipSuccess) return e;
         ag.x = a.wv.xd;
     }
-    if (a.max_groups > 0) launch_gemv<WT, EPI_GATEUP>(ag, s);
+    if (a.max_groups > 0 && skinny_path(a.T, a.H, a.I, WT, false)) {
+        if (hipError_t e = launch_skinny(ag, s, false); e != hipSuccess) return e;
+    } else if (a.max_groups > 0) launch_gemv<WT, EPI_GATEUP>(ag, s);
     else if (!a.wv.ypart) hipLaunchKernelGGL(zero_out, dim3(blocks), dim3(256), 0, s, a.out, n4);
     if (a.act_quant && a.max_groups > 0)
         if (hipError_t e = launch_act_quant_h(a, s); e != hipSuccess) return e;
     if (!prof.mark(2)) return hipErrorUnknown;
-    if (a.max_groups > 0) launch_gemv<WT, EPI_DOWN>(a, s);
+    if (a.max_groups > 0 && skinny_path(a.T, a.H, a.I, WT, true)) {
+        if (hipError_t e = launch_skinny(a, s, true); e != hipSuccess) return e;
+    } else if (a.max_groups > 0) launch_gemv<WT, EPI_DOWN>(a, s);
     if (!prof.mark(3)) return hipErrorUnknown;
     if (a.wv.ypart)
         hipLaunchKernelGGL(combine_kernel, dim3(blocks), dim3(256), 0, s, a.out, a.wv.ypart, a.ro.topk_slot, a.T,
@@ -628,21 +632,13 @@ static hipError_t launch_stream_path(const ExpertArgs &a, hipStream_t s, const P
     return hipGetLastError();
 }
 
-// Many-token chunks whose shapes tile evenly go to the MFMA GEMM.
-static bool gemm_path(const ExpertArgs &a) { return a.max_groups > 0 && gemm_shape(a.T, a.H, a.I, a.w_dtype); }
-
 hipError_t launch_experts(const ExpertArgs &a, hipStream_t s, const Prof &prof) {
+    if (a.max_groups > 0 && gemm_shape(a.T, a.H, a.I, a.w_dtype)) return launch_gemm(a, s, prof);
     switch (a.w_dtype) {
         case FT_DT_F32: return launch_stream_path<FT_DT_F32>(a, s, prof);
-        case FT_DT_BF16:
-            if (gemm_path(a)) return launch_gemm(a, s, prof);
-            return launch_stream_path<FT_DT_BF16>(a, s, prof);
-        case FT_DT_MXFP4:
-            if (gemm_path(a)) return launch_gemm(a, s, prof);
-            return launch_stream_path<FT_DT_MXFP4>(a, s, prof);
-        default:
-            if (gemm_path(a)) return launch_gemm(a, s, prof);
-            return launch_stream_path<FT_DT_FP8E4M3FN_B128>(a, s, prof);
+        case FT_DT_BF16: return launch_stream_path<FT_DT_BF16>(a, s, prof);
+        case FT_DT_MXFP4: return launch_stream_path<FT_DT_MXFP4>(a, s, prof);
+        default: return launch_stream_path<FT_DT_FP8E4M3FN_B128>(a, s, prof);
     }
 }
 

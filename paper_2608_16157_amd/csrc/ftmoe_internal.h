@@ -22,18 +22,10 @@ constexpr int kTokPerBlk = 16;          // tokens per workgroup in the multi-blo
 constexpr int kBlkPerPart = 16;         // router blocks per part of its scan (the part table)
 constexpr int kFusedMaxPairs = 2048;    // T*k handled by the single-workgroup router
 constexpr int kFusedMaxLds = 64 * 1024;
-#ifndef FT_GEMM_BM
-#define FT_GEMM_BM 128
-#endif
-#ifndef FT_GEMM_BN
-#define FT_GEMM_BN 256
-#endif
-constexpr int kGemmBM = FT_GEMM_BM;     // token rows per MFMA GEMM tile (prefill path)
-constexpr int kGemmBN = FT_GEMM_BN;     // weight rows per MFMA GEMM tile
-#ifndef FT_GEMM_MIN_TOKENS
-#define FT_GEMM_MIN_TOKENS 256
-#endif
-constexpr int kGemmMinTokens = FT_GEMM_MIN_TOKENS;   // token count from which the MFMA GEMM path is used
+constexpr int kGemmBM = 128;            // token rows per MFMA GEMM tile
+constexpr int kGemmBN = 256;            // weight rows per MFMA GEMM tile
+constexpr int kSkinnyRows = 64;         // most token rows of a skinny tile (skinny_tile.h)
+constexpr int kGemmMinTokens = 256;     // token count from which the matrix-core path's workspace and combine are used
 
 struct HostMailbox;   // a worker pool's device <-> host mailbox (defined with CpuPool)
 
@@ -57,11 +49,11 @@ struct RouteOut {
 struct WsView {
     int32_t *eff_slot;   // [E]
     int32_t *blk_hist;   // [nblk][E] per-block expert counts, then [ceil(nblk / kBlkPerPart)][E] part sums
-    int32_t *grp_meta;   // [8]: G (groups incl. shared), U (hit groups), n_hit, T, M-tiles
+    int32_t *grp_meta;   // [8]: G (groups incl. shared), U (hit groups), n_hit, T, M tiles, first skinny group
     int32_t *grp_slot;   // [E+1]
     int32_t *grp_beg;    // [E+1]
     int32_t *grp_len;    // [E+1]
-    int32_t *grp_mt_off; // [E+2] exclusive prefix of ceil(len / kGemmBM) over the groups
+    int32_t *grp_mt_off; // [E+2] exclusive prefix of ceil(len / kGemmBM) over the groups that are not skinny
     int32_t *mt_group;   // [max M tiles] group of each GEMM M tile
     int32_t *row_tok;    // [T*k + T]
     float *row_gate;     // [T*k + T]
@@ -83,6 +75,7 @@ struct RouteArgs {
     const float *logits;
     const int32_t *slot_table;
     int T, E, k, gating, n_slots, shared_slot, nbits, scan_parts;
+    int skinny_rows;   // groups of up to this many rows are skinny: numbered last, without M tiles
     RouteOut ro;
     WsView wv;
 };
@@ -97,6 +90,7 @@ struct ExpertArgs {
     int T, H, I, k, w_dtype, n_slots, shared;
     int act_quant;    // FT_ACT_*
     int max_groups;   // upper bound on groups, known on the host
+    int skinny_rows;  // matrix-core path: groups of up to this many rows go to the skinny tiles
     // routing of a one- or two-token call done by the gate/up kernel itself (logits != nullptr;
     // otherwise the router ran before and the workspace holds its groups)
     const float *logits;
@@ -115,8 +109,25 @@ struct WsLayout {
 // the launcher additionally needs at least one evaluation group.
 inline bool gemm_shape(int T, int H, int I, int w_dtype) {
     if (w_dtype == FT_DT_F32) return false;
-    if (w_dtype == FT_DT_MXFP4 && kGemmBN != 256) return false;   // its scale DMA assumes 256-row tiles
     return T >= kGemmMinTokens && H % kGemmBN == 0 && I % (kGemmBN / 2) == 0 && H <= 8192 && I <= 8192;
+}
+
+// Whether a projection of a streaming call of T tokens runs the skinny tiles (gemm.hip) instead of the
+// GEMV kernels; the two form the same sums in the same order.  The tiles win where groups hold enough
+// rows, or (MXFP4) the activations are large beside the weights, for their activations are read once
+// per 128 weight rows.  Measured per projection, GEMV against tiles in us: bf16 (Qwen3) gate/up 32
+// tokens 45 against 52, 64: 64.1 / 63.7, 72: 69.6 / 67.1, 160: 111 / 83, down 32: 27.8 / 27.5, 40:
+// 32.1 / 29.0, 160: 81 / 41; fp8 (DeepSeek-V3) gate/up 16: 152 / 156, 18: 163 / 162, 64: 265 / 239, down
+// 16: 81 / 82, 20: 91 / 86; MXFP4 (DeepSeek-V4-Flash) layer 3: 55.5 / 55.7, 5: 64.3 / 58.3, 32: 117 / 101.
+// K is bounded by the tiles' table of fp8 scales and their 32-bit weight offsets.
+inline bool skinny_path(int T, int H, int I, int w_dtype, bool down) {
+    if (w_dtype == FT_DT_F32 || T >= kGemmMinTokens || H > 8192 || I > 8192) return false;
+    const int min_tokens = w_dtype == FT_DT_MXFP4 ? 4 : w_dtype == FT_DT_FP8E4M3FN_B128 ? 17 : down ? 33 : 65;
+    return T >= min_tokens;
+}
+// Group rows up to which a group goes to the skinny tiles (the fp8 x fp8 kernels have none).
+inline int skinny_rows_of(int T, int act_quant) {
+    return act_quant != FT_ACT_EXACT && T >= kGemmMinTokens ? 0 : kSkinnyRows;
 }
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -297,7 +308,7 @@ void cpu_experts(const CpuExpertArgs &a);
 
 // Evaluation groups of a hybrid step from its routing after the cache plan (route.hip).
 struct RegroupArgs {
-    int E, T, k, shared_slot;
+    int E, T, k, shared_slot, skinny_rows;
     const int32_t *hit_off, *miss_off, *hit_pairs, *miss_pairs, *topk_slot;
     const float *topk_w;
     WsView wv;
@@ -308,6 +319,7 @@ hipError_t launch_route(const RouteArgs &a, hipStream_t s);
 hipError_t launch_cache_plan(const PlanArgs &a, hipStream_t s);
 hipError_t launch_experts(const ExpertArgs &a, hipStream_t s, const Prof &prof);
 hipError_t launch_gemm(const ExpertArgs &a, hipStream_t s, const Prof &prof);
+hipError_t launch_skinny(const ExpertArgs &a, hipStream_t s, bool down);
 // fp8 activations (quant.hip): x into codes and exponents (matrix-core path) or into quantised
 // bf16 (streaming path); h quantised in place (streaming path)
 hipError_t launch_act_quant_x(const ExpertArgs &a, hipStream_t s);

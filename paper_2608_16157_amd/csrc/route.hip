@@ -85,7 +85,7 @@ __device__ void scatter_run(int p0, int p1, int k, int nbits, const int32_t *__r
 // Exclusive scans of per-expert hit and miss totals, group table and counts.  Called by the
 // whole block after `s_tot` (pairs per expert) and `s_eff` are ready.  Writes hit_off/miss_off
 // to LDS (s_hoff/s_moff, E+1 entries) and global memory.
-__device__ void scan_experts(int E, int T, int k, int shared_slot, const int32_t *s_tot,
+__device__ void scan_experts(int E, int T, int k, int shared_slot, int skinny_rows, const int32_t *s_tot,
                              const int32_t *s_eff, int32_t *s_hoff, int32_t *s_moff,
                              int32_t *s_gidx, const int *s_status, const RouteOut &ro,
                              const WsView &wv) {
@@ -96,15 +96,16 @@ __device__ void scan_experts(int E, int T, int k, int shared_slot, const int32_t
         const int e0 = min(E, lane * epl), e1 = min(E, e0 + epl);
         // Evaluation groups are numbered, and their GEMM M tiles laid out, in classes: the shared
         // expert first, then the groups of several M tiles, then the one-tile groups by their
-        // live 32-row sub-tiles (4 down to 1), each class in expert order.  The GEMM launches a
-        // few hundred tiles at a time and skips the MFMAs of padding sub-tiles, so tiles of
-        // similar cost then share a launch (measured at DeepSeek-V3 prefill: layer 4.03 ->
-        // 3.90 ms together with the padding skip of the fp8 gate/up GEMM).
+        // live 32-row sub-tiles (4 down to 1), each class in expert order: the GEMM
+        // starts the longest tiles first, and neighbours cost about the same.  With skinny tiles
+        // (skinny_rows > 0) the classes of at most skinny_rows rows have no M tiles.
         auto cls = [&](int tot) {
             if (tot > kGemmBM) return 0;
             return 1 + min(3, (kGemmBM - tot) / 32);   // tot in (96, 128] -> 1, ..., (0, 32] -> 4
         };
         constexpr int NC = 5;
+        const int skinny_class = skinny_rows > 0 ? 3 : NC;   // classes 3 and 4: at most kSkinnyRows rows
+        static_assert(kSkinnyRows == 64 && kGemmBM == 128, "classes");
         uint32_t h = 0, m = 0, mx = 0, gc[NC] = {}, tc[NC] = {};
         for (int e = e0; e < e1; ++e) {
             const int tot = s_tot[e];
@@ -117,21 +118,23 @@ __device__ void scan_experts(int E, int T, int k, int shared_slot, const int32_t
 #pragma unroll
                 for (int i = 0; i < NC; ++i) {
                     gc[i] += i == c ? 1u : 0u;
-                    tc[i] += i == c ? static_cast<uint32_t>((tot + kGemmBM - 1) / kGemmBM) : 0u;
+                    tc[i] += i == c && i < skinny_class ? static_cast<uint32_t>((tot + kGemmBM - 1) / kGemmBM) : 0u;
                 }
             }
         }
         const uint32_t hi = wave_incl_scan_u32(h), mi = wave_incl_scan_u32(m), xi = wave_incl_scan_u32(mx);
-        const uint32_t smt = shared_slot >= 0 ? (T + kGemmBM - 1) / kGemmBM : 0;
-        const uint32_t sh = shared_slot >= 0 ? 1u : 0u;   // the shared expert is group 0
-        uint32_t grun[NC], trun[NC], U = 0, MT = 0;
+        // the shared expert is group 0, or the last one if skinny itself
+        const uint32_t sh = shared_slot >= 0 && T > skinny_rows ? 1u : 0u;
+        const uint32_t smt = sh ? (T + kGemmBM - 1) / kGemmBM : 0;
+        uint32_t grun[NC], trun[NC], U = 0, MT = 0, g_skinny = 0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             const uint32_t gi = wave_incl_scan_u32(gc[i]), ti = wave_incl_scan_u32(tc[i]);
             grun[i] = sh + U + gi - gc[i];
-            trun[i] = sh * smt + MT + ti - tc[i];
+            trun[i] = smt + MT + ti - tc[i];
             U += readlane_u32(gi, kWave - 1);
             MT += readlane_u32(ti, kWave - 1);
+            if (i < skinny_class) g_skinny = sh + U;
         }
         uint32_t hrun = hi - h, mrun = mi - m;
         for (int e = e0; e < e1; ++e) {
@@ -151,9 +154,11 @@ __device__ void scan_experts(int E, int T, int k, int shared_slot, const int32_t
                         trun[i] += (tot + kGemmBM - 1) / kGemmBM;
                     }
                 s_gidx[e] = static_cast<int>(gg);
-                wv.grp_mt_off[gg] = tt;
-                const int nmt = (tot + kGemmBM - 1) / kGemmBM;
-                for (int i = 0; i < nmt; ++i) wv.mt_group[tt + i] = gg;
+                if (c < skinny_class) {
+                    wv.grp_mt_off[gg] = tt;
+                    const int nmt = (tot + kGemmBM - 1) / kGemmBM;
+                    for (int i = 0; i < nmt; ++i) wv.mt_group[tt + i] = gg;
+                }
             }
             hrun += hit ? tot : 0;
             mrun += hit ? 0 : tot;
@@ -173,14 +178,16 @@ __device__ void scan_experts(int E, int T, int k, int shared_slot, const int32_t
             wv.grp_meta[2] = nh;
             wv.grp_meta[3] = T;
             wv.grp_meta[4] = MT + smt;
+            wv.grp_meta[5] = g_skinny;
             if (shared_slot >= 0) {
-                wv.grp_slot[0] = shared_slot;
-                wv.grp_beg[0] = nh;
-                wv.grp_len[0] = T;
-                wv.grp_mt_off[0] = 0;
+                const uint32_t gs = sh ? 0 : U;
+                wv.grp_slot[gs] = shared_slot;
+                wv.grp_beg[gs] = nh;
+                wv.grp_len[gs] = T;
+                if (sh) wv.grp_mt_off[0] = 0;
                 for (uint32_t i = 0; i < smt; ++i) wv.mt_group[i] = 0;
             }
-            wv.grp_mt_off[G] = MT + smt;
+            wv.grp_mt_off[g_skinny] = MT + smt;
         }
     }
     __syncthreads();
@@ -194,7 +201,6 @@ __device__ void scan_experts(int E, int T, int k, int shared_slot, const int32_t
             wv.grp_len[g] = s_tot[e];
         }
     }
-    // list tails and the shared expert's rows
     // the list tails and the shared expert's rows are written by route_scatter, spread over its
     // workgroups
 }
@@ -389,7 +395,9 @@ __global__ __launch_bounds__(kFusedThreads) void route_fused(RouteArgs a) {
             for (int c = 0; c < nch; ++c) tot += s_wh[c * E + e];
             return tot;
         };
-        uint32_t h = 0, m = 0, g = 0, mx = 0, mtl = 0;
+        // groups: those with M tiles first, then the skinny ones, each kind in expert order (the
+        // shared expert is the first of its kind's, or the last of all if skinny itself)
+        uint32_t h = 0, m = 0, gl = 0, gs = 0, mx = 0, mtl = 0;
 #pragma unroll
         for (int i = 0; i < kMaxEpl; ++i) {
             const int e = e0 + i;
@@ -402,14 +410,18 @@ __global__ __launch_bounds__(kFusedThreads) void route_fused(RouteArgs a) {
             const bool hit = slot >= 0;
             h += hit ? tot : 0;
             m += hit ? 0 : tot;
-            g += (hit && tot > 0) ? 1 : 0;
+            gl += (hit && tot > a.skinny_rows) ? 1 : 0;
+            gs += (hit && tot > 0 && tot <= a.skinny_rows) ? 1 : 0;
             mx += (!hit && tot > 0) ? 1 : 0;
-            mtl += hit ? (tot + kGemmBM - 1) / kGemmBM : 0;
+            mtl += (hit && tot > a.skinny_rows) ? (tot + kGemmBM - 1) / kGemmBM : 0;
         }
         const uint32_t hi = wave_incl_scan_u32(h), mi = wave_incl_scan_u32(m);
-        const uint32_t gi = wave_incl_scan_u32(g), xi = wave_incl_scan_u32(mx);
+        const uint32_t gli = wave_incl_scan_u32(gl), gsi = wave_incl_scan_u32(gs), xi = wave_incl_scan_u32(mx);
         const uint32_t ti = wave_incl_scan_u32(mtl);
-        uint32_t hrun = hi - h, mrun = mi - m, grun = gi - g, trun = ti - mtl;
+        const uint32_t sh = a.shared_slot >= 0 && T > a.skinny_rows ? 1u : 0u;
+        const uint32_t smt = sh ? (T + kGemmBM - 1) / kGemmBM : 0;
+        const uint32_t GL = sh + readlane_u32(gli, kWave - 1), U = GL - sh + readlane_u32(gsi, kWave - 1);
+        uint32_t hrun = hi - h, mrun = mi - m, lrun = sh + gli - gl, srun = GL + gsi - gs, trun = smt + ti - mtl;
 #pragma unroll
         for (int i = 0; i < kMaxEpl; ++i) {
             const int e = e0 + i;
@@ -428,20 +440,22 @@ __global__ __launch_bounds__(kFusedThreads) void route_fused(RouteArgs a) {
             a.ro.hit_off[e] = hrun;
             a.ro.miss_off[e] = mrun;
             if (hit && tot > 0) {
-                a.wv.grp_slot[grun] = slot;
-                a.wv.grp_beg[grun] = hrun;
-                a.wv.grp_len[grun] = tot;
-                a.wv.grp_mt_off[grun] = trun;
-                const int nmt = (tot + kGemmBM - 1) / kGemmBM;
-                for (int u = 0; u < nmt; ++u) a.wv.mt_group[trun + u] = grun;
+                const uint32_t gg = tot > a.skinny_rows ? lrun++ : srun++;
+                a.wv.grp_slot[gg] = slot;
+                a.wv.grp_beg[gg] = hrun;
+                a.wv.grp_len[gg] = tot;
+                if (tot > a.skinny_rows) {
+                    a.wv.grp_mt_off[gg] = trun;
+                    const int nmt = (tot + kGemmBM - 1) / kGemmBM;
+                    for (int u = 0; u < nmt; ++u) a.wv.mt_group[trun + u] = gg;
+                    trun += nmt;
+                }
             }
             hrun += hit ? tot : 0;
             mrun += hit ? 0 : tot;
-            grun += (hit && tot > 0) ? 1 : 0;
-            trun += hit ? (tot + kGemmBM - 1) / kGemmBM : 0;
         }
         const uint32_t nh = readlane_u32(hi, kWave - 1), nm = readlane_u32(mi, kWave - 1);
-        const uint32_t U = readlane_u32(gi, kWave - 1), mexp = readlane_u32(xi, kWave - 1);
+        const uint32_t mexp = readlane_u32(xi, kWave - 1);
         const uint32_t MT = readlane_u32(ti, kWave - 1);
         if (lane == kWave - 1) {
             s_hoff[E] = nh;
@@ -453,21 +467,21 @@ __global__ __launch_bounds__(kFusedThreads) void route_fused(RouteArgs a) {
             a.ro.counts[2] = mexp;
             a.ro.counts[3] = *s_status;
             const int shared = a.shared_slot;
-            const uint32_t smt = shared >= 0 ? (T + kGemmBM - 1) / kGemmBM : 0;
-            const uint32_t G = U + (shared >= 0 ? 1 : 0);
-            a.wv.grp_meta[0] = G;
+            a.wv.grp_meta[0] = U + (shared >= 0 ? 1 : 0);
             a.wv.grp_meta[1] = U;
             a.wv.grp_meta[2] = nh;
             a.wv.grp_meta[3] = T;
             a.wv.grp_meta[4] = MT + smt;
+            a.wv.grp_meta[5] = GL;
             if (shared >= 0) {
-                a.wv.grp_slot[U] = shared;
-                a.wv.grp_beg[U] = nh;
-                a.wv.grp_len[U] = T;
-                a.wv.grp_mt_off[U] = MT;
-                for (uint32_t i = 0; i < smt; ++i) a.wv.mt_group[MT + i] = U;
+                const uint32_t g = sh ? 0 : U;
+                a.wv.grp_slot[g] = shared;
+                a.wv.grp_beg[g] = nh;
+                a.wv.grp_len[g] = T;
+                if (sh) a.wv.grp_mt_off[0] = 0;
+                for (uint32_t i = 0; i < smt; ++i) a.wv.mt_group[i] = 0;
             }
-            a.wv.grp_mt_off[G] = MT + smt;
+            a.wv.grp_mt_off[GL] = MT + smt;
         }
         chunk_prefix();
     }
@@ -613,7 +627,7 @@ __global__ __launch_bounds__(1024) void route_scan(RouteArgs a, int nblk) {
         a.wv.eff_slot[x] = s_eff[x];
     }
     __syncthreads();
-    scan_experts(E, a.T, a.k, a.shared_slot, s_tot, s_eff, s_hoff, s_moff, s_gidx, s_status, a.ro, a.wv);
+    scan_experts(E, a.T, a.k, a.shared_slot, a.skinny_rows, s_tot, s_eff, s_hoff, s_moff, s_gidx, s_status, a.ro, a.wv);
     __syncthreads();
     if (active) {
         int run = s_part[part * E + e] + (s_eff[e] >= 0 ? s_hoff[e] : s_moff[e]);
@@ -727,9 +741,9 @@ static hipError_t launch_route_npl(RouteArgs a, hipStream_t s) {
 // map and row arrays as the router, in expert-id order, then the shared expert's rows.
 // One 1024-thread workgroup, thread e = expert e.
 __global__ __launch_bounds__(1024) void regroup_kernel(RegroupArgs a) {
-    __shared__ int32_t s_beg[kMaxExperts + 1];   // first row of group g
-    __shared__ int32_t s_src[kMaxExperts];       // list position of group g's first pair (miss list: + T*k)
-    __shared__ uint32_t s_wsum[3][1024 / kWave];
+    __shared__ int32_t s_beg[kMaxExperts + 1];   // first row of the i-th expert with a group
+    __shared__ int32_t s_src[kMaxExperts];       // list position of its first pair (miss list: + T*k)
+    __shared__ uint32_t s_wsum[4][1024 / kWave];
     __shared__ int32_t s_tot[4];
     const int E = a.E, T = a.T, k = a.k, tid = threadIdx.x;
     const int lane = lane_id(), wv = tid / kWave;
@@ -752,31 +766,42 @@ __global__ __launch_bounds__(1024) void regroup_kernel(RegroupArgs a) {
     }
     const uint32_t in_g = n > 0 ? 1u : 0u;
     const uint32_t rows = static_cast<uint32_t>(n);
-    const uint32_t mts = in_g ? static_cast<uint32_t>((n + kGemmBM - 1) / kGemmBM) : 0u;
-    // ---- block-wide exclusive scans of (group flag, rows, M tiles) over the experts
+    const uint32_t large = n > a.skinny_rows ? 1u : 0u;   // a group with M tiles (numbered first)
+    const uint32_t mts = large ? static_cast<uint32_t>((n + kGemmBM - 1) / kGemmBM) : 0u;
+    // ---- block-wide exclusive scans of (group flag, rows, M tiles, large flag) over the experts
     const uint32_t gi = wave_incl_scan_u32(in_g), ri = wave_incl_scan_u32(rows), ti = wave_incl_scan_u32(mts);
+    const uint32_t li = wave_incl_scan_u32(large);
     if (lane == kWave - 1) {
         s_wsum[0][wv] = gi;
         s_wsum[1][wv] = ri;
         s_wsum[2][wv] = ti;
+        s_wsum[3][wv] = li;
     }
     __syncthreads();
-    uint32_t gb = 0, rb = 0, tb = 0;
-    for (int w = 0; w < wv; ++w) {
-        gb += s_wsum[0][w];
-        rb += s_wsum[1][w];
-        tb += s_wsum[2][w];
+    uint32_t gb = 0, rb = 0, tb = 0, lb = 0, GL = 0;
+    for (int w = 0; w < 1024 / kWave; ++w) {
+        GL += s_wsum[3][w];
+        if (w < wv) {
+            gb += s_wsum[0][w];
+            rb += s_wsum[1][w];
+            tb += s_wsum[2][w];
+            lb += s_wsum[3][w];
+        }
     }
-    const int g = static_cast<int>(gb + gi - in_g), r0 = static_cast<int>(rb + ri - rows),
-              t0 = static_cast<int>(tb + ti - mts);
+    // the shared expert is the first group, or the last one if skinny itself
+    const uint32_t sh = a.shared_slot >= 0 && T > a.skinny_rows ? 1u : 0u;
+    const uint32_t smt = sh ? (T + kGemmBM - 1) / kGemmBM : 0;
+    const int at0 = static_cast<int>(gb + gi - in_g), r0 = static_cast<int>(rb + ri - rows);
+    const uint32_t t0 = smt + tb + ti - mts, l0 = lb + li - large;
     if (in_g) {
+        const uint32_t g = sh + (large ? l0 : GL + at0 - l0);
         a.wv.grp_slot[g] = slot;
         a.wv.grp_beg[g] = r0;
         a.wv.grp_len[g] = n;
-        a.wv.grp_mt_off[g] = t0;
+        if (large) a.wv.grp_mt_off[g] = t0;
         for (uint32_t i = 0; i < mts; ++i) a.wv.mt_group[t0 + i] = g;
-        s_beg[g] = r0;
-        s_src[g] = src;
+        s_beg[at0] = r0;
+        s_src[at0] = src;
     }
     if (tid == 1023) {
         // totals over every wave: thread 1023 is the last lane of the last wave
@@ -789,27 +814,27 @@ __global__ __launch_bounds__(1024) void regroup_kernel(RegroupArgs a) {
         s_tot[0] = static_cast<int>(U);
         s_tot[1] = static_cast<int>(NR);
         s_beg[U] = static_cast<int>(NR);
-        const uint32_t smt = a.shared_slot >= 0 ? (T + kGemmBM - 1) / kGemmBM : 0;
-        const uint32_t G = U + (a.shared_slot >= 0 ? 1 : 0);
-        a.wv.grp_meta[0] = G;
+        a.wv.grp_meta[0] = U + (a.shared_slot >= 0 ? 1 : 0);
         a.wv.grp_meta[1] = U;
         a.wv.grp_meta[2] = NR;
         a.wv.grp_meta[3] = T;
         a.wv.grp_meta[4] = MT + smt;
+        a.wv.grp_meta[5] = sh + GL;
         if (a.shared_slot >= 0) {
-            a.wv.grp_slot[U] = a.shared_slot;
-            a.wv.grp_beg[U] = NR;
-            a.wv.grp_len[U] = T;
-            a.wv.grp_mt_off[U] = MT;
-            for (uint32_t i = 0; i < smt; ++i) a.wv.mt_group[MT + i] = U;
+            const uint32_t g = sh ? 0 : U;
+            a.wv.grp_slot[g] = a.shared_slot;
+            a.wv.grp_beg[g] = NR;
+            a.wv.grp_len[g] = T;
+            if (sh) a.wv.grp_mt_off[0] = 0;
+            for (uint32_t i = 0; i < smt; ++i) a.wv.mt_group[i] = 0;
         }
-        a.wv.grp_mt_off[G] = MT + smt;
+        a.wv.grp_mt_off[sh + GL] = MT + smt;
     }
     __syncthreads();
-    // ---- rows: row r of group g is pair i = r - beg(g) of its list
+    // ---- rows: row r of an expert is pair i = r - beg of its list
     const int U = s_tot[0], NR = s_tot[1];
     for (int r = tid; r < NR; r += 1024) {
-        int lo = 0, hi = U - 1;           // the last group whose first row is <= r
+        int lo = 0, hi = U - 1;           // the last expert whose first row is <= r
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (s_beg[mid] <= r) lo = mid;

@@ -265,9 +265,10 @@ __device__ __forceinline__ void route_wave_body(const RouteArgs &a, int32_t *lds
     if (act && prank == __popcll(same) - 1) s_tot[pe] = prank + 1;
     wave_lds_sync();
 
-    // exclusive scans over the experts: list offsets, groups, GEMM tile map, counts
+    // exclusive scans over the experts: list offsets, groups, counts (so few tokens never run the GEMM,
+    // which would need the M tile map)
     int tots[NPL];
-    uint32_t h = 0, m = 0, g = 0, mx = 0, mtl = 0;
+    uint32_t h = 0, m = 0, g = 0, mx = 0;
 #pragma unroll
     for (int i = 0; i < NPL; ++i) {
         const int e = e0 + i;
@@ -277,12 +278,10 @@ __device__ __forceinline__ void route_wave_body(const RouteArgs &a, int32_t *lds
         m += hit ? 0 : tots[i];
         g += (hit && tots[i] > 0) ? 1 : 0;
         mx += (!hit && tots[i] > 0) ? 1 : 0;
-        mtl += hit ? (tots[i] + kGemmBM - 1) / kGemmBM : 0;
     }
     const uint32_t hi = wave_incl_scan_u32(h), mi = wave_incl_scan_u32(m);
     const uint32_t gi = wave_incl_scan_u32(g), xi = wave_incl_scan_u32(mx);
-    const uint32_t ti = wave_incl_scan_u32(mtl);
-    uint32_t hrun = hi - h, mrun = mi - m, grun = gi - g, trun = ti - mtl;
+    uint32_t hrun = hi - h, mrun = mi - m, grun = gi - g;
 #pragma unroll
     for (int i = 0; i < NPL; ++i) {
         const int e = e0 + i;
@@ -300,9 +299,6 @@ __device__ __forceinline__ void route_wave_body(const RouteArgs &a, int32_t *lds
                 a.wv.grp_slot[grun] = slot[i];
                 a.wv.grp_beg[grun] = hrun;
                 a.wv.grp_len[grun] = tot;
-                a.wv.grp_mt_off[grun] = trun;
-                const int nmt = (tot + kGemmBM - 1) / kGemmBM;
-                for (int u = 0; u < nmt; ++u) a.wv.mt_group[trun + u] = grun;
             }
             if constexpr (FUSED) {
                 sink.slot[grun] = slot[i];
@@ -313,11 +309,9 @@ __device__ __forceinline__ void route_wave_body(const RouteArgs &a, int32_t *lds
         hrun += hit ? tot : 0;
         mrun += hit ? 0 : tot;
         grun += (hit && tot > 0) ? 1 : 0;
-        trun += hit ? (tot + kGemmBM - 1) / kGemmBM : 0;
     }
     const uint32_t nh = readlane_u32(hi, kWave - 1), nm = readlane_u32(mi, kWave - 1);
     const uint32_t U = readlane_u32(gi, kWave - 1), mexp = readlane_u32(xi, kWave - 1);
-    const uint32_t MT = readlane_u32(ti, kWave - 1);
     if (lane == kWave - 1) {
         const int shared = a.shared_slot;
         const uint32_t G = U + (shared >= 0 ? 1 : 0);
@@ -338,21 +332,16 @@ __device__ __forceinline__ void route_wave_body(const RouteArgs &a, int32_t *lds
         a.ro.counts[1] = nm;
         a.ro.counts[2] = mexp;
         a.ro.counts[3] = *s_status;
-        const uint32_t smt = shared >= 0 ? (T + kGemmBM - 1) / kGemmBM : 0;
         const uint32_t G = U + (shared >= 0 ? 1 : 0);
         a.wv.grp_meta[0] = G;
         a.wv.grp_meta[1] = U;
         a.wv.grp_meta[2] = nh;
         a.wv.grp_meta[3] = T;
-        a.wv.grp_meta[4] = MT + smt;
         if (shared >= 0) {
             a.wv.grp_slot[U] = shared;
             a.wv.grp_beg[U] = nh;
             a.wv.grp_len[U] = T;
-            a.wv.grp_mt_off[U] = MT;
-            for (uint32_t i = 0; i < smt; ++i) a.wv.mt_group[MT + i] = U;
         }
-        a.wv.grp_mt_off[G] = MT + smt;
     }
     wave_lds_sync();
 
