@@ -2,12 +2,13 @@
 // permutation (Section 3.2: router and cache lookup on the GPU; Section 4.1: routed logical ids
 // rewritten into slot ids or a CPU flag, kept as fixed-shape buffers with device counts).
 //
-// Three variants:
+// Four variants:
 //  * route_wave: one wave does everything (one or two tokens, T*k <= 64 pairs).  A layer call of
 //    one or two tokens over 65 to 256 experts runs the same body inside its gate/up kernel
 //    instead (route_wave.h, experts.hip): every workgroup routes for itself, one writes the outputs.
 //  * route_fused: one 1024-thread workgroup does everything in LDS (decode), for the larger
 //    decode batches after route_topk has selected every token's experts on many CUs.
+//  * route_tokens -> route_place: more tokens (prompt chunks up to 2048 tokens).
 //  * route_tokens -> route_partscan -> route_scan -> route_scatter: many tokens (prefill chunks).
 // All produce bit-identical outputs: the permutation is a counting sort whose within-expert
 // order is the pair index, computed with wave ballots, never with order-dependent atomics.
@@ -532,15 +533,17 @@ __global__ __launch_bounds__(kWave) void route_wave(RouteArgs a) {
 
 // ---------------------------------------------------------------------------------------
 // Multi-workgroup routing.  Block b owns tokens [b*kTokPerBlk, (b+1)*kTokPerBlk).
+// With few blocks (route_place's range) a block has one wave per token, which leaves no wave several
+// selections in a row; with many, four waves per block fill the chip.
 template <int NPL>
-__global__ __launch_bounds__(256) void route_tokens(RouteArgs a) {
+__global__ __launch_bounds__(kTokPerBlk * kWave) void route_tokens(RouteArgs a) {
     __shared__ int32_t s_hist[kMaxExperts];
     const int E = a.E, k = a.k, T = a.T;
     for (int e = threadIdx.x; e < E; e += blockDim.x) s_hist[e] = 0;
     __syncthreads();
     const int wave = threadIdx.x / kWave, lane = lane_id();
     const int t0 = blockIdx.x * kTokPerBlk;
-    for (int t = t0 + wave; t < min(T, t0 + kTokPerBlk); t += 4) {
+    for (int t = t0 + wave; t < min(T, t0 + kTokPerBlk); t += blockDim.x / kWave) {
         int id;
         float w;
         wave_topk<NPL>(a.logits + static_cast<size_t>(t) * E, E, k, a.gating, id, w);
@@ -683,6 +686,106 @@ __global__ __launch_bounds__(64) void route_scatter(RouteArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
+// For up to kMaxPlaceBlks router blocks: route_partscan, route_scan and route_scatter in one launch.
+// Every workgroup scans the whole block table for itself (at most 128 rows, 32 or fewer per thread at
+// 256 experts, all in flight at once) and places its own block's pairs; workgroup 0 also writes the
+// offsets, counts and groups.  A scan in a workgroup of its own costs launches and several dependent
+// rounds of global memory more: routing stage (with its events) at Qwen3 777 tokens 25.8 -> 15.5 us,
+// DeepSeek-V3 300 tokens 31.3 -> 18.6, 2048 tokens 33.3 -> 19.3, DeepSeek-V4-Flash 1500 tokens 31.8 ->
+// 19.4 (of which route_tokens with a wave per token 3.5 to 4.5).
+__global__ __launch_bounds__(1024) void route_place(RouteArgs a) {
+    extern __shared__ int32_t lds[];
+    const int E = a.E, k = a.k, T = a.T, nblk = gridDim.x, blk = blockIdx.x, tid = threadIdx.x;
+    int32_t *s_raw = lds, *s_eff = s_raw + E, *s_tot = s_eff + E, *s_hoff = s_tot + E;
+    int32_t *s_moff = s_hoff + E + 1, *s_gidx = s_moff + E + 1, *s_run = s_gidx + E;
+    int *s_status = s_run + E;
+    int32_t *s_part = s_status + 1;                        // [parts][E] pairs of a range of blocks
+    int32_t *s_pre = s_part + a.scan_parts * E;            // [parts][E] of them, before this block
+    int32_t *s_ids = s_pre + a.scan_parts * E;             // this block's pairs
+    float *s_w = reinterpret_cast<float *>(s_ids + kTokPerBlk * k);
+    int32_t *s_cnt = reinterpret_cast<int32_t *>(s_w + kTokPerBlk * k);   // [min(n_slots, kSlotCountCap)]
+    const int t0 = blk * kTokPerBlk, t1 = min(T, t0 + kTokPerBlk), p0 = t0 * k, p1 = t1 * k;
+    const int raw = tid < E ? a.slot_table[tid] : -1;
+    // (a block has at most kTokPerBlk * kMaxTopK = 1024 pairs)
+    const int my = min(p0 + tid, p1 - 1), my_id = a.ro.topk_ids[my];
+    const float my_w = a.ro.topk_w[my];
+    const int parts = a.scan_parts, e = tid % E, part = tid / E;
+    const int per = (nblk + parts - 1) / parts;
+    const int b0 = min(nblk, part * per), b1 = min(nblk, b0 + per);
+    if (tid == 0) *s_status = 0;
+    if (p0 + tid < p1) {
+        s_ids[tid] = my_id;
+        s_w[tid] = my_w;
+    }
+    if (part < parts) {
+        int sum = 0, pre = 0;
+        constexpr int kBatch = 32;
+        for (int b = b0; b < b1; b += kBatch) {
+            int buf[kBatch];
+            // clamped, unconditional loads; entries past the range count 0
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) buf[i] = a.wv.blk_hist[static_cast<size_t>(min(b + i, b1 - 1)) * E + e];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                sum += b + i < b1 ? buf[i] : 0;
+                pre += b + i < min(b1, blk) ? buf[i] : 0;
+            }
+        }
+        s_part[part * E + e] = sum;
+        s_pre[part * E + e] = pre;
+    }
+    validate_slots(raw, E, a.n_slots, a.shared_slot, s_raw, s_cnt, s_eff, s_status);
+    for (int x = tid; x < E; x += blockDim.x) {
+        int sum = 0, pre = 0;
+        for (int q = 0; q < parts; ++q) {
+            sum += s_part[q * E + x];
+            pre += s_pre[q * E + x];
+        }
+        s_tot[x] = sum;
+        s_run[x] = pre;
+    }
+    __syncthreads();
+    if (blk == 0) {
+        scan_experts(E, T, k, a.shared_slot, a.skinny_rows, s_tot, s_eff, s_hoff, s_moff, s_gidx, s_status, a.ro, a.wv);
+    } else if (tid < kWave) {
+        // the offsets alone: lane l owns experts [l*epl, l*epl + epl)
+        const int epl = (E + kWave - 1) / kWave, e0 = min(E, tid * epl), e1 = min(E, e0 + epl);
+        uint32_t h = 0, m = 0;
+        for (int x = e0; x < e1; ++x) (s_eff[x] >= 0 ? h : m) += s_tot[x];
+        const uint32_t hi = wave_incl_scan_u32(h), mi = wave_incl_scan_u32(m);
+        uint32_t hrun = hi - h, mrun = mi - m;
+        for (int x = e0; x < e1; ++x) {
+            s_hoff[x] = hrun;
+            s_moff[x] = mrun;
+            (s_eff[x] >= 0 ? hrun : mrun) += s_tot[x];
+        }
+        if (tid == kWave - 1) {
+            s_hoff[E] = hi;
+            s_moff[E] = mi;
+        }
+    }
+    __syncthreads();
+    for (int x = tid; x < E; x += blockDim.x) s_run[x] += s_eff[x] >= 0 ? s_hoff[x] : s_moff[x];
+    const int nh = s_hoff[E], nm = s_moff[E];
+    __syncthreads();
+    if (tid < kWave) {
+        scatter_run(p0, p1, k, a.nbits, s_ids - p0, s_w - p0, s_eff, s_run, a.ro, a.wv);
+        return;
+    }
+    for (int i = p0 + tid - kWave; i < p1; i += blockDim.x - kWave) {
+        if (i >= nh) a.ro.hit_pairs[i] = -1;
+        if (i >= nm) a.ro.miss_pairs[i] = -1;
+    }
+    if (a.shared_slot >= 0) {
+        for (int t = t0 + tid - kWave; t < t1; t += blockDim.x - kWave) {
+            a.wv.row_tok[nh + t] = t;
+            a.wv.row_pair[nh + t] = T * k + t;
+            a.wv.row_gate[nh + t] = 1.0f;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------
 // Top-k ahead of route_fused<NPL, true> for the larger decode batches: one wave per token, four
 // tokens per workgroup, so the k selection rounds of all tokens run on many CUs at once instead
 // of in turn on the 16 waves of the fused router.
@@ -722,8 +825,15 @@ static hipError_t launch_route_npl(RouteArgs a, hipStream_t s) {
     }
     const int nblk = (a.T + kTokPerBlk - 1) / kTokPerBlk;
     const int nparts = (nblk + kBlkPerPart - 1) / kBlkPerPart;
+    a.scan_parts = max(1, min(1024 / a.E, nblk));
+    const int place_lds = 4 * (7 * a.E + 3 + 2 * a.scan_parts * a.E + 2 * kTokPerBlk * a.k + ncnt);
+    const bool place = nblk <= kMaxPlaceBlks && place_lds <= kFusedMaxLds;
+    hipLaunchKernelGGL(route_tokens<NPL>, dim3(nblk), dim3(place ? kTokPerBlk * kWave : 256), 0, s, a);
+    if (place) {
+        hipLaunchKernelGGL(route_place, dim3(nblk), dim3(1024), place_lds, s, a);
+        return hipGetLastError();
+    }
     a.scan_parts = max(1, min(1024 / a.E, nparts));
-    hipLaunchKernelGGL(route_tokens<NPL>, dim3(nblk), dim3(256), 0, s, a);
     hipLaunchKernelGGL(route_partscan, dim3(nparts, (a.E + 255) / 256), dim3(256), 0, s, a, nblk);
     const int scan_lds = 4 * (6 * a.E + 3 + a.scan_parts * a.E + ncnt);
     hipLaunchKernelGGL(route_scan, dim3(1), dim3(1024), scan_lds, s, a, nblk);
