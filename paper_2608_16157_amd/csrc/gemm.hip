@@ -137,6 +137,7 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
     static_assert(!kFp8 || 128 % BK == 0, "an fp8 K stage lies in one scale block");
     constexpr int kStagesPerKb = kFp8 ? 128 / BK : 1;
     constexpr int kMaxKb = 64;                       // K <= 8192
+    constexpr int kMaxStages = 6;                    // of the ring
     // The ring: as many stages as fit the LDS left by the tables, two workgroups to a CU.  A tile
     // with ML live 32-row sub-tiles stages only those rows, so thin tiles get a deeper ring.
     constexpr int kTables = (kFp8 ? 16 * kGemmWaves * kMaxKb : 0) + (kAq ? kBM * kMaxKb + 4 * kGemmWaves * kBM + 4 * kBM : 0) +
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
     __shared__ float s_gate[kBM];
     // fp8 activations: e8m0 scale byte of each tile row and K block, and (gate/up epilogue) the
     // per-wave largest |h| of each row and the rows' h exponents
-    __shared__ uint8_t s_ascale[kAq ? kBM * kMaxKb : 1];
+    __shared__ __attribute__((aligned(256))) uint8_t s_ascale[kAq ? kBM * kMaxKb : 1];
     __shared__ float s_hmax[kAq ? kGemmWaves : 1][kAq ? kBM : 1];
     __shared__ int32_t s_hexp[kAq ? kBM : 1];
 
@@ -257,7 +258,78 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
             xcol[j] = 256 * (2 * fq + half) + r;
         }
     }
-    const int nkb = K / 128;
+    const int nk = K / BK, nkb = K / 128;
+    // ---- gate/up: the first stages are requested before the tables below are looked up, so that the
+    // two latencies overlap.  (The tables' waits then cover all of these stages: little beside gate/up's
+    // long K loop, but on the down projection waiting for the first stage alone is better.)  Together
+    // with the exponents by DMA, DeepSeek-V3 with fp8 activations: gate/up 2048 tokens 920 -> 880 us,
+    // 8192 tokens 1.92 -> 1.80 ms; down with the early request 502 -> 523 us.
+    const int mlive = __builtin_amdgcn_readfirstlane((min(len - m0, kBM) + 31) / 32);   // live 32-row sub-tiles
+    constexpr int A_MAX = ASUB * kMI / 1024 / kGemmWaves;   // A DMA instructions per wave and stage, at most
+    const int a_tot = mlive * (ASUB / 1024);                // and of the tile
+    // A instruction ii of this wave: where the instructions do not split evenly, some are done
+    // twice (the same bytes to the same place), which keeps every wave's count equal
+    const uint8_t *asrc[A_MAX];
+    uint32_t alds[A_MAX];
+#pragma unroll
+    for (int ii = 0; ii < A_MAX; ++ii) {
+        const int idx = (wave + kGemmWaves * ii) % a_tot;
+        const int row = idx * A_ROWS + lane / A_CHUNKS;
+        const int r = min(len - 1, m0 + row);      // padding rows repeat the last row; never stored
+        constexpr size_t EB = kAq ? 1 : 2;   // bytes per activation element
+        const uint8_t *rowp;
+        if constexpr (EPI == GEMM_GATEUP)
+            rowp = (kAq ? a.wv.xq : static_cast<const uint8_t *>(a.x)) + static_cast<size_t>(a.wv.row_tok[beg + r]) * H * EB;
+        else
+            rowp = (kAq ? a.wv.hq : static_cast<const uint8_t *>(a.wv.h)) + static_cast<size_t>(beg + r) * I * EB;
+        asrc[ii] = rowp + (swz<ARB>(row, lane % A_CHUNKS) << 4);
+        alds[ii] = idx * 1024;
+    }
+    // fp8 activations: each tile row's exponent byte of every K block (rows of x by token, rows of h by
+    // position), 64 bytes a row; where a row's bytes are whole words they come by DMA, 4 rows at a time
+    constexpr int X_MAX = kAq ? kBM / 4 / kGemmWaves : 1;
+    const uint8_t *esrc[X_MAX];
+    const bool ewords = nkb % 4 == 0;
+    if constexpr (kAq) {
+#pragma unroll
+        for (int ii = 0; ii < X_MAX; ++ii) {
+            const int r = min(len - 1, m0 + (wave + kGemmWaves * ii) * 4 + lane / 16);
+            const size_t srow = EPI == GEMM_GATEUP ? static_cast<size_t>(a.wv.row_tok[beg + r]) : static_cast<size_t>(beg + r);
+            esrc[ii] = (EPI == GEMM_GATEUP ? a.wv.xs : a.wv.hs) + srow * nkb + 4 * min(lane % 16, nkb / 4 - 1);
+        }
+    }
+    const uint32_t lring = lds_address(s_ring);
+    auto issue = [&](auto apw, int kt, uint32_t so, uint32_t asz) {
+        const uint32_t l = lring + so;
+#pragma unroll
+        for (int ii = 0; ii < A_MAX; ++ii)
+            if (ii < apw) dma16(asrc[ii] + static_cast<size_t>(kt) * ARB, l + alds[ii]);
+        const uint8_t *bs = bexp + static_cast<size_t>(kt) * BRB;
+#pragma unroll
+        for (int ii = 0; ii < B_INSTR; ++ii) dma16(bs, boff[ii], l + asz + (wave * B_INSTR + ii) * 1024);
+        if constexpr (kFp4)
+            dma4(xexp + static_cast<size_t>(kt) * (BK / 32) * nrows, xoff, l + asz + BSTAGE + wave * 256);
+    };
+    constexpr bool kEarly = EPI == GEMM_GATEUP;
+    if constexpr (kEarly) {
+        const int asz = mlive * ASUB, stg = asz + BSTAGE + XSTAGE, ns = min(kMaxStages, kRing / stg);
+        for (int st = 0; st < ns; ++st) issue((a_tot + kGemmWaves - 1) / kGemmWaves, min(st, nk - 1), st * stg, asz);
+    }
+    if constexpr (kAq) {
+        if (ewords) {
+            const uint32_t le = lds_address(s_ascale);
+#pragma unroll
+            for (int ii = 0; ii < X_MAX; ++ii)
+                if (ii < 2 * mlive) dma4(esrc[ii], le + (wave + kGemmWaves * ii) * 256);
+        } else {
+            const uint8_t *src = EPI == GEMM_GATEUP ? a.wv.xs : a.wv.hs;
+            for (int idx = t; idx < 32 * mlive * nkb; idx += kGemmThreads) {
+                const int r = idx / nkb, kb = idx - r * nkb, rr = min(len - 1, m0 + r);
+                const size_t srow = EPI == GEMM_GATEUP ? static_cast<size_t>(a.wv.row_tok[beg + rr]) : static_cast<size_t>(beg + rr);
+                s_ascale[r * kMaxKb + kb] = src[srow * nkb + kb];
+            }
+        }
+    }
     // fp8 block-scale tables of each wave's columns (gate half and up half of a gate/up tile; one
     // block for down), staged in LDS before the pipeline starts: a vector load inside the loop
     // would make the compiler drain the DMA stages.  Lane kb of each wave holds
@@ -292,17 +364,6 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
         }
         if (lane == 0) s_zeroblk[wn] = zero != 0;
     }
-    // fp8 activations: each tile row's exponent byte of every K block (rows of x by token, rows
-    // of h by position), staged like the weight scales before the pipeline starts
-    if constexpr (kAq) {
-        const uint8_t *src = EPI == GEMM_GATEUP ? a.wv.xs : a.wv.hs;
-        for (int idx = t; idx < kBM * nkb; idx += kGemmThreads) {
-            const int r = idx / nkb, kb = idx - r * nkb;
-            const int rr = min(len - 1, m0 + r);
-            const size_t srow = EPI == GEMM_GATEUP ? static_cast<size_t>(a.wv.row_tok[beg + rr]) : static_cast<size_t>(beg + rr);
-            s_ascale[r * kMaxKb + kb] = src[srow * nkb + kb];
-        }
-    }
     // token and gate of each row of the tile (down projection epilogue)
     if constexpr (EPI == GEMM_DOWN) {
         for (int i = t; i < kBM; i += kGemmThreads) {
@@ -312,7 +373,6 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
         }
     }
 
-    const int nk = K / BK;
     constexpr int KS = kAq ? BK / 64 : BK / 16;   // MFMA sub-steps per K stage
     // Operands of one 32x32x16 MFMA sub-step.  The lane (r = lane % 32, kg = lane / 32) holds 8 K
     // values of row r for each operand; which 8 is free as long as A and B agree.  bf16 weights:
@@ -484,7 +544,6 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
             if constexpr (kReads > kPairs) __builtin_amdgcn_sched_group_barrier(0x100, kReads - kPairs, 0);
         }
     };
-    const uint32_t lring = lds_address(s_ring);
     // One tile with ML live sub-tiles: the K loop and the epilogue, instantiated together (a common
     // epilogue would merge the accumulators of all instances, whose copies then spilled).
     auto tile = [&](auto ml, auto zs) {
@@ -497,42 +556,11 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
 #pragma unroll
             for (int j = 0; j < kNJ; ++j) acc[i][j] = floatx16_t{};
         constexpr int ASZ = ML * ASUB, STG = ASZ + BSTAGE + XSTAGE;
-        constexpr int NSR = kRing / STG, NS = NSR < 6 ? NSR : 6;      // ring depth
+        constexpr int NSR = kRing / STG, NS = NSR < kMaxStages ? NSR : kMaxStages;   // ring depth
         constexpr int A_TOT = ASZ / 1024;                             // A DMA instructions per stage
         constexpr int A_PW = (A_TOT + kGemmWaves - 1) / kGemmWaves;   // and per wave
         constexpr int PER_STAGE = A_PW + B_INSTR + (kFp4 ? 1 : 0);
         static_assert(NS >= 2 && NS * PER_STAGE < 64, "ring depth, vmcnt range");
-        // A instruction ii of this wave: where the instructions do not split evenly, some are done
-        // twice (the same bytes to the same place), which keeps every wave's count equal
-        const uint8_t *asrc[A_PW];
-        uint32_t alds[A_PW];
-#pragma unroll
-        for (int ii = 0; ii < A_PW; ++ii) {
-            const int idx = (wave + kGemmWaves * ii) % A_TOT;
-            const int row = idx * A_ROWS + lane / A_CHUNKS;
-            const int r = min(len - 1, m0 + row);      // padding rows repeat the last row; never stored
-            constexpr size_t EB = kAq ? 1 : 2;   // bytes per activation element
-            const uint8_t *rowp;
-            if constexpr (EPI == GEMM_GATEUP)
-                rowp = (kAq ? a.wv.xq : static_cast<const uint8_t *>(a.x)) +
-                       static_cast<size_t>(a.wv.row_tok[beg + r]) * H * EB;
-            else
-                rowp = (kAq ? a.wv.hq : static_cast<const uint8_t *>(a.wv.h)) + static_cast<size_t>(beg + r) * I * EB;
-            asrc[ii] = rowp + (swz<ARB>(row, lane % A_CHUNKS) << 4);
-            alds[ii] = idx * 1024;
-        }
-        auto issue = [&](int kt, uint32_t so) {
-            const uint32_t l = lring + so;
-#pragma unroll
-            for (int ii = 0; ii < A_PW; ++ii) dma16(asrc[ii] + static_cast<size_t>(kt) * ARB, l + alds[ii]);
-            const uint8_t *bs = bexp + static_cast<size_t>(kt) * BRB;
-#pragma unroll
-            for (int ii = 0; ii < B_INSTR; ++ii) dma16(bs, boff[ii], l + ASZ + (wave * B_INSTR + ii) * 1024);
-            if constexpr (kFp4)
-                dma4(xexp + static_cast<size_t>(kt) * (BK / 32) * nrows, xoff, l + ASZ + BSTAGE + wave * 256);
-        };
-#pragma unroll
-        for (int st = 0; st < NS; ++st) issue(min(st, nk - 1), st * STG);
         Frag cur, nxt;
         uint32_t so = 0, sn = STG;   // ring offsets of stage kt and of the next one
         // stage kt, the I-th of an unrolled turn; fp8 K blocks open at the stages with I * BK = 0
@@ -546,8 +574,13 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
                     wait_vmcnt<(NS - 2) * PER_STAGE>();
                     wait_lgkmcnt0();
                     stage_barrier();
-                    issue(min(kt + NS, nk - 1), so);
+                    issue(ic<A_PW>{}, min(kt + NS, nk - 1), so, ASZ);
                 }
+                // The sub-steps before the hand-off outrank the CU's other workgroup, whose loads and
+                // hand-offs then fall into this one's MFMAs: gate/up at 8192 tokens DeepSeek-V3 2.34 ->
+                // 2.30 ms, DeepSeek-V4-Flash 812 -> 787 us; the other kernels lost or kept their time.
+                constexpr bool kPrio = EPI == GEMM_GATEUP && (kWiden8 || kFp4);
+                if constexpr (kPrio && KSI == 0) __builtin_amdgcn_s_setprio(1);
                 __builtin_amdgcn_sched_barrier(0);
                 constexpr int kRescale = (kOpens && KSI == 0) ? 1 : 0;
                 mma(acc, cur, ks, ml, zs, ic<kRescale>{});
@@ -556,14 +589,19 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
                           KSI + 1 < KS ? kt : min(kt + 1, nk - 1));
                 interleave(ic<(KSI + 1) % KS>{}, ml, zs, ic<kRescale>{});
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (kPrio && KSI + 2 == KS) __builtin_amdgcn_s_setprio(0);
                 cur = nxt;
             });
             so = sn;
             sn = sn + STG == NS * STG ? 0 : sn + STG;
         };
-        wait_vmcnt<(NS - 1) * PER_STAGE>();
-        wait_lgkmcnt0();
-        stage_barrier();
+        if constexpr (!kEarly) {
+#pragma unroll
+            for (int st = 0; st < NS; ++st) issue(ic<A_PW>{}, min(st, nk - 1), st * STG, ASZ);
+            wait_vmcnt<(NS - 1) * PER_STAGE>();
+            wait_lgkmcnt0();
+            stage_barrier();
+        }
         load_frag(s_ring, s_ring + ASZ, s_ring + ASZ + BSTAGE, ic<0>{}, ml, zs, cur, cur, 0);
         for (int kt0 = 0; kt0 < nk; kt0 += kStagesPerKb)
             static_for<0, kStagesPerKb>([&](auto i) { stage(i, kt0 + decltype(i)::value); });
@@ -651,15 +689,14 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
         }
     };
 
-    // outstanding stores of the zeroing loop must not count against the DMA waits below; the
-    // barrier publishes the staged scale / token / gate tables
+    // the tables (gate/up: and the first stages) have landed, and the stores of the zeroing loop, which
+    // must not count against the DMA waits of the main loop
     wait_vmcnt<0>();
     __syncthreads();
     bool any_zero_scale = false;
     if constexpr (kFp8)
         for (int w = 0; w < kGemmWaves; ++w) any_zero_scale |= s_zeroblk[w] != 0;
     // one instance per live sub-tile count
-    const int mlive = __builtin_amdgcn_readfirstlane((min(len - m0, kBM) + 31) / 32);
     static_for<1, kMI + 1>([&](auto q) {
         constexpr int ML = decltype(q)::value;
         if (mlive == ML) {

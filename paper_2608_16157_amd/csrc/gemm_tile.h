@@ -96,6 +96,11 @@ __device__ __forceinline__ int scalar_load(const int32_t *p) {
     return __builtin_amdgcn_readfirstlane(*(const __attribute__((address_space(4))) int32_t *)p);
 }
 
+__device__ __forceinline__ void dma4(const uint8_t *g, uint32_t lds) {
+    lds = __builtin_amdgcn_readfirstlane(lds);
+    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(lds) : "memory");
+}
+
 // LDS byte address of a shared object, for the DMAs
 __device__ __forceinline__ uint32_t lds_address(uint8_t *p) {
     return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t *)p));
