@@ -104,11 +104,12 @@ def algorithmic_work(lay, route, act_quant=0):
 
 def kernel_source_sha(kernel: str) -> str:
     """Hash of the sources a dominant kernel is built from (its traffic figures are tied to it):
-    the GEMM's or the GEMV's file plus the shared device and interface headers, and for the GEMM
-    the router, whose tile map orders its tiles."""
+    the GEMM's or the GEMV's files plus the shared device and interface headers, and for the GEMM
+    the router, whose group order and tile map order its tiles."""
     import hashlib
     h = hashlib.sha256()
-    files = ("gemm.hip", "route.hip", "route_wave.h") if "gemm" in kernel else ("experts.hip", "route_wave.h")
+    files = (("gemm.hip", "gemm_tile.h", "skinny_tile.h", "route.hip", "route_wave.h") if "gemm" in kernel
+             else ("experts.hip", "route_wave.h"))
     for name in (*files, "ftmoe_device.h", "ftmoe_internal.h"):
         with open(os.path.join(ROOT, "paper_2608_16157_amd", "csrc", name), "rb") as fh:
             h.update(name.encode() + b"\0" + fh.read())
@@ -661,7 +662,10 @@ def measure_forward(config, T, n_layers, steps, warmup, hip, combine=0, act_quan
                 "bytes_per_launch": round(gu_bytes), "ms_per_launch": round(gu_ms, 5)}
     else:
         achieved = gu_bytes / (gu_ms / 1e3) / 1e9
-        roof = {"kernel": "grouped gate/up GEMV + SiLU-mul (grouped_gemv<gate/up>)", "bound": "hbm",
+        # the library's rule for the few-row tiles (skinny_path)
+        tiles = T >= {0: 256, 1: 65, 2: 17, 3: 4}[cfg.w_dtype]
+        roof = {"kernel": "grouped gate/up few-row tiles + SiLU-mul (skinny_gemm<gate/up>)" if tiles else
+                          "grouped gate/up GEMV + SiLU-mul (grouped_gemv<gate/up>)", "bound": "hbm",
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "bytes_per_launch": round(gu_bytes), "ms_per_launch": round(gu_ms, 5)}
