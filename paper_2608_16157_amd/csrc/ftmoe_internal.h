@@ -20,7 +20,7 @@ constexpr int kMaxExperts = 1024;
 constexpr int kMaxTopK = 64;
 constexpr int kTokPerBlk = 16;          // tokens per workgroup in the multi-block router
 constexpr int kBlkPerPart = 16;         // router blocks per part of its scan (the part table)
-constexpr int kMaxPlaceBlks = 128;      // router blocks up to which route_place takes the scan and the scatter
+constexpr int kMaxPlaceBlks = 256;      // router blocks up to which route_place takes the scan and the scatter
 constexpr int kFusedMaxPairs = 2048;    // T*k handled by the single-workgroup router
 constexpr int kFusedMaxLds = 64 * 1024;
 constexpr int kGemmBM = 128;            // token rows per MFMA GEMM tile

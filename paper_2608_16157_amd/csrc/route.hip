@@ -8,7 +8,7 @@
 //    instead (route_wave.h, experts.hip): every workgroup routes for itself, one writes the outputs.
 //  * route_fused: one 1024-thread workgroup does everything in LDS (decode), for the larger
 //    decode batches after route_topk has selected every token's experts on many CUs.
-//  * route_tokens -> route_place: more tokens (prompt chunks up to 2048 tokens).
+//  * route_tokens -> route_place: more tokens (prompt chunks up to 4096 tokens).
 //  * route_tokens -> route_partscan -> route_scan -> route_scatter: many tokens (prefill chunks).
 // All produce bit-identical outputs: the permutation is a counting sort whose within-expert
 // order is the pair index, computed with wave ballots, never with order-dependent atomics.
@@ -687,12 +687,15 @@ __global__ __launch_bounds__(64) void route_scatter(RouteArgs a) {
 
 // ---------------------------------------------------------------------------------------
 // For up to kMaxPlaceBlks router blocks: route_partscan, route_scan and route_scatter in one launch.
-// Every workgroup scans the whole block table for itself (at most 128 rows, 32 or fewer per thread at
-// 256 experts, all in flight at once) and places its own block's pairs; workgroup 0 also writes the
+// Every workgroup scans the whole block table for itself (at most 256 rows, 32 or fewer per thread at
+// 128 experts, two batches of 32 at 256) and places its own block's pairs; workgroup 0 also writes the
 // offsets, counts and groups.  A scan in a workgroup of its own costs launches and several dependent
 // rounds of global memory more: routing stage (with its events) at Qwen3 777 tokens 25.8 -> 15.5 us,
 // DeepSeek-V3 300 tokens 31.3 -> 18.6, 2048 tokens 33.3 -> 19.3, DeepSeek-V4-Flash 1500 tokens 31.8 ->
-// 19.4 (of which route_tokens with a wave per token 3.5 to 4.5).
+// 19.4 (of which route_tokens with a wave per token 3.5 to 4.5); 4096 tokens, layer: Qwen3 457 -> 450 us,
+// DeepSeek-V3 2454 -> 2391, DeepSeek-V4-Flash 862 -> 853 (routing 34 -> 20, 46 -> 33, 40 -> 25).  The
+// blocks' reads of the table grow with the square of the tokens: at 8192 tokens (512 blocks) the gain is
+// gone already with 128 experts (Qwen3 layer 755 us either way).
 __global__ __launch_bounds__(1024) void route_place(RouteArgs a) {
     extern __shared__ int32_t lds[];
     const int E = a.E, k = a.k, T = a.T, nblk = gridDim.x, blk = blockIdx.x, tid = threadIdx.x;

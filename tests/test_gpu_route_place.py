@@ -17,8 +17,10 @@ pytestmark = pytest.mark.gpu
     (128, 8, 257, False, True),
     (3, 3, 700, True, False),       # many scanning threads per expert
     (1000, 5, 500, True, False),    # one scanning thread per expert
-    (256, 6, 2048, False, False),   # 128 blocks
-    (256, 6, 2049, True, False),    # one block too many
+    (256, 6, 2048, False, False),   # 32 rows of the table per scanning thread
+    (256, 6, 2049, True, False),    # a second batch of rows
+    (256, 6, 4096, False, False),   # 256 blocks
+    (128, 8, 4097, True, False),    # one block too many
 ])
 def test_route_place(E, k, T, shared, ties):
     lay = workloads.random_layer(E + T, hidden=128, inter=128, n_experts=E, top_k=k, tokens=T,
