@@ -66,11 +66,13 @@ __device__ __forceinline__ int swz(int r, int c) {
 // the compiler makes every later LDS read wait for all outstanding DMAs into the same LDS object,
 // and the rings here are one object whose slots are chosen at run time.  The instructions have no
 // register outputs; the waits are the explicit ones of the main loops (loads return in order, so
-// waits that the compiler adds for its own loads are at worst longer than needed).  M0 is set by
-// each instruction for itself; nothing else in these kernels uses it.
+// waits that the compiler adds for its own loads are at worst longer than needed).  Each sets M0, the
+// LDS address, for itself (nothing else in these kernels uses it; the compiler reserves it and takes
+// no clobber of it); the ISA asks for one wait state between that write and the DMA, which neither
+// the hardware checks nor the compiler inserts inside an assembly string.
 __device__ __forceinline__ void dma16(const uint8_t *g, uint32_t lds) {
     lds = __builtin_amdgcn_readfirstlane(lds);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds) : "memory");
 }
 // the same with a wave-uniform base and a 32-bit offset per lane
 __device__ __forceinline__ const uint8_t *uniform_ptr(const uint8_t *p) {
@@ -82,12 +84,12 @@ __device__ __forceinline__ const uint8_t *uniform_ptr(const uint8_t *p) {
 __device__ __forceinline__ void dma16(const uint8_t *base, uint32_t off, uint32_t lds) {
     base = uniform_ptr(base);
     lds = __builtin_amdgcn_readfirstlane(lds);
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
 }
 __device__ __forceinline__ void dma4(const uint8_t *base, uint32_t off, uint32_t lds) {
     base = uniform_ptr(base);
     lds = __builtin_amdgcn_readfirstlane(lds);
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" : : "v"(off), "s"(base), "s"(lds) : "memory");
 }
 
 // A load through the scalar cache from a wave-uniform address of memory that this kernel does not
@@ -98,7 +100,7 @@ __device__ __forceinline__ int scalar_load(const int32_t *p) {
 
 __device__ __forceinline__ void dma4(const uint8_t *g, uint32_t lds) {
     lds = __builtin_amdgcn_readfirstlane(lds);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(lds) : "memory");
 }
 
 // LDS byte address of a shared object, for the DMAs
