@@ -123,6 +123,10 @@ void decode_row(const CpuBank &bank, int w_dtype, int nrows, int K, int r, float
         const float *sc = static_cast<const float *>(bank.s) + static_cast<size_t>(r / 128) * (K / 128);
         for (int cb = 0; cb < K / 128; ++cb) {
             const float s = sc[cb];
+            if (s == 0.0f) {   // adds nothing, whatever its codes hold, as on the GPU
+                std::memset(dst + cb * 128, 0, 128 * sizeof(float));
+                continue;
+            }
             for (int c = cb * 128; c < cb * 128 + 128; ++c) dst[c] = table.v[src[c]] * s;
         }
     }

@@ -85,6 +85,24 @@ def test_cpu_experts_is_thread_count_independent():
     assert all(torch.equal(outs[0], o) for o in outs[1:])
 
 
+def test_cpu_experts_fp8_zero_scale_blocks():
+    """A block of fp8 weights with scale 0 contributes nothing, whatever its codes hold (NaN codes here),
+    as on the GPU."""
+    lay, pool = _pool_case(11, workloads.DT_FP8, 0, 4, 2, 5, 256, 384)
+    pool["s13"][:, 1, 0] = pool["s2"][:, 0, 2] = 0
+    pool["w13"][:, 128:256, :128] = pool["w2"][:, :128, 256:] = 0
+    desc = lay.desc()
+    r = oracle.route(desc, lay.logits.numpy(), lay.slot_table.numpy())
+    banks = {"w13": to_np_bits(pool["w13"]), "w2": to_np_bits(pool["w2"]), "s13": pool["s13"].numpy(), "s2": pool["s2"].numpy()}
+    table = np.arange(4, dtype=np.int32)
+    ref, _ = oracle.moe_partial(dict(desc, n_slots=4, shared_slot=-1), banks, lay.logits.numpy(), table, to_np_bits(lay.x))
+    pool["w13"][:, 128:256, :128] = pool["w2"][:, :128, 256:] = 0x7F
+    out = torch.empty(5, 256, dtype=torch.float32)
+    ftm.ft_cpu_experts(desc, pool, lay.x, 5, torch.tensor(r["topk_ids"], dtype=torch.int32),
+                       torch.tensor(r["topk_w"], dtype=torch.float32), torch.arange(4, dtype=torch.int32), out)
+    assert oracle.max_rel_err(out.numpy(), ref) <= TOL[workloads.DT_FP8]
+
+
 def test_cpu_experts_rejects_bad_lists():
     lay, pool = _pool_case(5, workloads.DT_BF16, 0, 8, 2, 3, 128, 128)
     desc = lay.desc()
