@@ -120,6 +120,10 @@ __device__ __forceinline__ int mixed_tile(int b, int nl, int ns) {
     return i < cl ? ql * x + min(x, rl) + i : ~(qs * x + __popc(more & ((1u << x) - 1u)) + i - cl);
 }
 
+// The grid's first dimension is at most this many blocks: one dimension holds fewer than 2^32 threads,
+// and the largest call (1048576 tokens of 65 experts, H = 8192) has 17 million down tiles.
+constexpr int kGridXLog = 22;
+
 template <int WT, int EPI>
 __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArgs a, int ntn) {
     constexpr bool kAq = WT == kWtFp8Act;                          // fp8 activations (fp8 x fp8 MFMA)
@@ -159,25 +163,25 @@ __global__ __launch_bounds__(kGemmThreads, kGemmOcc) void grouped_gemm(ExpertArg
     __shared__ float s_hmax[kAq ? kGemmWaves : 1][kAq ? kBM : 1];
     __shared__ int32_t s_hexp[kAq ? kBM : 1];
 
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, blk = static_cast<int>(blockIdx.y << kGridXLog | blockIdx.x);
     if constexpr (EPI == GEMM_GATEUP) {
         // zero the output that the down projection accumulates into
         const size_t n4 = static_cast<size_t>(a.T) * a.H / 4;
         float4 *o4 = reinterpret_cast<float4 *>(a.out);
-        for (size_t i = static_cast<size_t>(blockIdx.x) * kGemmThreads + t; i < n4;
-             i += static_cast<size_t>(gridDim.x) * kGemmThreads)
+        for (size_t i = static_cast<size_t>(blk) * kGemmThreads + t; i < n4;
+             i += static_cast<size_t>(gridDim.x) * gridDim.y * kGemmThreads)
             o4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     // tile of this block: L among the large tiles, or ~L among the skinny ones
     const int nlarge = scalar_load(a.wv.grp_meta + 4) * ntn;
     int L;
     if constexpr (kAq) {
-        if (static_cast<int>(blockIdx.x) >= nlarge) return;
-        L = xcd_remap(blockIdx.x, nlarge);
+        if (blk >= nlarge) return;
+        L = xcd_remap(blk, nlarge);
     } else {
         const int nskinny = (scalar_load(a.wv.grp_meta) - scalar_load(a.wv.grp_meta + 5)) * (kBN / kSkinnyBN) * ntn;
-        if (static_cast<int>(blockIdx.x) >= nlarge + nskinny) return;
-        L = mixed_tile(blockIdx.x, nlarge, nskinny);
+        if (blk >= nlarge + nskinny) return;
+        L = mixed_tile(blk, nlarge, nskinny);
     }
     L = __builtin_amdgcn_readfirstlane(L);
     if constexpr (!kAq) {
@@ -718,8 +722,9 @@ static void launch_tiles(const ExpertArgs &a, hipStream_t s) {
     // one ragged tile per group of more than skinny_rows rows) and skinny ones
     const long large = (rows / kBM + std::min<long>(a.max_groups, rows / (a.skinny_rows + 1))) * ntn;
     const long skinny = a.skinny_rows > 0 ? static_cast<long>(a.max_groups) * (kBN / kSkinnyBN) * ntn : 0;
-    hipLaunchKernelGGL((grouped_gemm<WT, EPI>), dim3(static_cast<unsigned>(large + skinny)), dim3(kGemmThreads), 0, s, a,
-                       ntn);
+    const long n = large + skinny, gx = std::min(n, 1L << kGridXLog);
+    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>((n + gx - 1) / gx));
+    hipLaunchKernelGGL((grouped_gemm<WT, EPI>), grid, dim3(kGemmThreads), 0, s, a, ntn);
 }
 
 template <int WT>
