@@ -119,12 +119,22 @@ inline bool gemm_shape(int T, int H, int I, int w_dtype) {
 // per 128 weight rows.  Measured per projection, GEMV against tiles in us: bf16 (Qwen3) gate/up 32
 // tokens 45 against 52, 64: 64.1 / 63.7, 72: 69.6 / 67.1, 160: 111 / 83, down 32: 27.8 / 27.5, 40:
 // 32.1 / 29.0, 160: 81 / 41; fp8 (DeepSeek-V3) gate/up 16: 152 / 156, 18: 163 / 162, 64: 265 / 239, down
-// 16: 81 / 82, 20: 91 / 86; MXFP4 (DeepSeek-V4-Flash) layer 3: 55.5 / 55.7, 5: 64.3 / 58.3, 32: 117 / 101.
-// K is bounded by the tiles' table of fp8 scales and their 32-bit weight offsets.
+// 16: 81 / 82, 20: 91 / 86; MXFP4 (DeepSeek-V4-Flash) layer 3: 55.5 / 55.7, 5: 64.3 / 58.3, 32: 117 / 101;
+// its down projection alone at 4 and 6 tokens -2 and -4 % of the layer, at 7 +1 % (4096 x 7168, 8 experts: 4
+// tokens -13 %, 7: +1 %).  Over 15 more layer shapes (8 to 1024 experts, uniform and Zipf 1.2 routing) the
+// limits hold to within 5 % of the layer, but for weight rows a multiple of 4096 bytes apart: the 128 row
+// pieces of a stage then begin in the same few memory channels.  There, in % of the layer, uniform /
+// Zipf routing: fp8 H = 4096 (3968, 4224: 0 to +6) gate/up 24 tokens -11 / -14, 64: -8 / -2, 96: -8 / +4, 128:
+// -7 / +7; bf16 H = 2048 (1920, 2176: +2 to +13) 65: -5 / -5, 96: -5 / +4, 192: -3 / +15; MXFP4 I = 8192 down 10:
+// -15 / -18, 64: -7 / 0, 128: -7 / +32.  The bf16 down projection keeps its limit (I = 2048, 33: -2 / +2, 65: 0 / +5).
+// Below, K is the projection's (H, or I of the down projection); it is bounded by the tiles' table of
+// fp8 scales and their 32-bit weight offsets.
 inline bool skinny_path(int T, int H, int I, int w_dtype, bool down) {
     if (w_dtype == FT_DT_F32 || T >= kGemmMinTokens || H > 8192 || I > 8192) return false;
-    const int min_tokens = w_dtype == FT_DT_MXFP4 ? 4 : w_dtype == FT_DT_FP8E4M3FN_B128 ? 17 : down ? 33 : 65;
-    return T >= min_tokens;
+    const bool bf16 = w_dtype == FT_DT_BF16, fp4 = w_dtype == FT_DT_MXFP4;
+    const int K = down ? I : H, row_bytes = bf16 ? 2 * K : fp4 ? K / 2 : K;
+    if (row_bytes % 4096 == 0 && !(bf16 && down)) return T >= 96;
+    return T >= (bf16 ? (down ? 33 : 65) : fp4 ? (down ? 7 : 4) : 17);
 }
 // Group rows up to which a group goes to the skinny tiles (the fp8 x fp8 kernels have none).
 inline int skinny_rows_of(int T, int act_quant) {

@@ -1,6 +1,15 @@
 """Marshalling between the synthetic torch layers and the oracle's numpy arrays."""
+import atexit
+import functools
+import os
+import shutil
+import subprocess
+import tempfile
+
 import numpy as np
 import torch
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def to_np_bits(t: torch.Tensor) -> np.ndarray:
@@ -40,3 +49,26 @@ def decode_bank_torch(bank: torch.Tensor, w_dtype: int, scales=None) -> torch.Te
     v = bank.view(torch.float8_e4m3fn).to(torch.float64)
     s = scales.double().repeat_interleave(128, 0).repeat_interleave(128, 1)
     return v * s
+
+
+@functools.lru_cache(maxsize=None)
+def _rule_program() -> str:
+    """A host program around the library's rule for the few-row tiles (one line in, one line out)."""
+    d = tempfile.mkdtemp(prefix="ftmoe_rule_")
+    atexit.register(shutil.rmtree, d, ignore_errors=True)
+    src, exe = os.path.join(d, "rule.cpp"), os.path.join(d, "rule")
+    with open(src, "w") as fh:
+        fh.write('#include "ftmoe_internal.h"\n#include <cstdio>\n'
+                 'int main() { int T, H, I, w, d;\n'
+                 '  while (std::scanf("%d %d %d %d %d", &T, &H, &I, &w, &d) == 5)\n'
+                 '    std::printf("%d\\n", ftmoe::skinny_path(T, H, I, w, d)); }\n')
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2608_16157_amd", "csrc"), src, "-o", exe], check=True)
+    return exe
+
+
+def few_row_tiles(cases):
+    """Whether the library runs few-row tiles (else a GEMV), for each (T, H, I, w_dtype, down)."""
+    text = "".join(" ".join(str(int(v)) for v in c) + "\n" for c in cases)
+    out = subprocess.run([_rule_program()], input=text, capture_output=True, text=True, check=True).stdout
+    return [bool(int(v)) for v in out.split()]
