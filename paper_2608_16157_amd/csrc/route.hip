@@ -50,8 +50,8 @@ __device__ void validate_slots(int raw, int E, int n_slots, int shared_slot, int
     __syncthreads();
 }
 
-// Scatter one wave's contiguous run of pairs [p0, p1) in pair order.  `run` holds, per expert,
-// the next free position in the hit or miss list for this run (LDS, private to the wave).
+// Scatter one wave's contiguous run of pairs [p0, p1) in pair order; `ids` and `w` hold that run.  `run`
+// holds, per expert, the next free position in the hit or miss list for this run (LDS, private to the wave).
 __device__ void scatter_run(int p0, int p1, int k, int nbits, const int32_t *__restrict__ ids,
                             const float *__restrict__ w, const int32_t *__restrict__ s_eff,
                             int32_t *run, const RouteOut &ro, const WsView &wv) {
@@ -59,7 +59,7 @@ __device__ void scatter_run(int p0, int p1, int k, int nbits, const int32_t *__r
     for (int base = p0; base < p1; base += kWave) {
         const int p = base + lane;
         const bool act = p < p1;
-        const int e = act ? ids[p] : 0;
+        const int e = act ? ids[p - p0] : 0;
         const uint64_t same = match_lanes(static_cast<uint32_t>(e), nbits, __ballot(act));
         const int rank = __popcll(same & lanemask_lt());
         const int cnt = __popcll(same);
@@ -75,7 +75,7 @@ __device__ void scatter_run(int p0, int p1, int k, int nbits, const int32_t *__r
                 ro.hit_pairs[pos] = p;
                 wv.row_tok[pos] = p / k;
                 wv.row_pair[pos] = p;
-                wv.row_gate[pos] = w[p];
+                wv.row_gate[pos] = w[p - p0];
             } else {
                 ro.miss_pairs[pos] = p;
             }
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(64) void route_scatter(RouteArgs a) {
     __syncthreads();
     const int t0 = blockIdx.x * kTokPerBlk, t1 = min(T, t0 + kTokPerBlk);
     const int p0 = t0 * k, p1 = t1 * k;
-    scatter_run(p0, p1, k, a.nbits, a.ro.topk_ids, a.ro.topk_w, s_eff, s_run, a.ro, a.wv);
+    scatter_run(p0, p1, k, a.nbits, a.ro.topk_ids + p0, a.ro.topk_w + p0, s_eff, s_run, a.ro, a.wv);
     for (int i = p0 + static_cast<int>(threadIdx.x); i < p1; i += blockDim.x) {
         if (i >= nh) a.ro.hit_pairs[i] = -1;
         if (i >= nm) a.ro.miss_pairs[i] = -1;
@@ -772,7 +772,7 @@ __global__ __launch_bounds__(1024) void route_place(RouteArgs a) {
     const int nh = s_hoff[E], nm = s_moff[E];
     __syncthreads();
     if (tid < kWave) {
-        scatter_run(p0, p1, k, a.nbits, s_ids - p0, s_w - p0, s_eff, s_run, a.ro, a.wv);
+        scatter_run(p0, p1, k, a.nbits, s_ids, s_w, s_eff, s_run, a.ro, a.wv);
         return;
     }
     for (int i = p0 + tid - kWave; i < p1; i += blockDim.x - kWave) {
