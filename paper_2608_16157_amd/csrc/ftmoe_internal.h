@@ -26,6 +26,7 @@ constexpr int kFusedMaxLds = 64 * 1024;
 constexpr int kGemmBM = 128;            // token rows per MFMA GEMM tile
 constexpr int kGemmBN = 256;            // weight rows per MFMA GEMM tile
 constexpr int kSkinnyRows = 64;         // most token rows of a skinny tile (skinny_tile.h)
+constexpr int kSkinnyMinTokens = 4;     // fewest tokens of a call that takes skinny tiles (skinny_path)
 constexpr int kGemmMinTokens = 256;     // token count from which the matrix-core path's workspace and combine are used
 
 struct HostMailbox;   // a worker pool's device <-> host mailbox (defined with CpuPool)
@@ -44,11 +45,15 @@ struct RouteOut {
 
 // Views into the caller's workspace.
 //  rows: the hit list positions 0..n_hit-1 followed by T rows of the shared expert; row r
-//  evaluates token row_tok[r] with gate row_gate[r].  Groups: one per hit expert (ascending
-//  expert id) and then the shared expert; group g covers rows [grp_beg[g], +grp_len[g]) and
-//  reads the weights of bank row grp_slot[g].
+//  evaluates token row_tok[r] with gate row_gate[r].  Groups: one per hit expert and one of the shared
+//  expert; group g covers rows [grp_beg[g], +grp_len[g]) and reads the weights of bank row grp_slot[g].
+//  Rows are in expert order, groups are not: those of more than skinny_rows rows come first (the shared
+//  expert's ahead of them), then the skinny ones (the shared expert's last).  Inside either kind the
+//  order is that of the experts, or of cost classes (scan_experts).  The one-wave router of one or two
+//  tokens keeps expert order with the shared expert last, and writes neither the M tile map (grp_mt_off,
+//  mt_group) nor grp_meta[4] and [5]: no call that small runs a kernel that reads them.
 struct WsView {
-    int32_t *eff_slot;   // [E]
+    int32_t *eff_slot;   // [E] (written and read by the four-launch router only)
     int32_t *blk_hist;   // [nblk][E] per-block expert counts, then [ceil(nblk / kBlkPerPart)][E] part sums
     int32_t *grp_meta;   // [8]: G (groups incl. shared), U (hit groups), n_hit, T, M tiles, first skinny group
     int32_t *grp_slot;   // [E+1]
@@ -134,7 +139,7 @@ inline bool skinny_path(int T, int H, int I, int w_dtype, bool down) {
     const bool bf16 = w_dtype == FT_DT_BF16, fp4 = w_dtype == FT_DT_MXFP4;
     const int K = down ? I : H, row_bytes = bf16 ? 2 * K : fp4 ? K / 2 : K;
     if (row_bytes % 4096 == 0 && !(bf16 && down)) return T >= 96;
-    return T >= (bf16 ? (down ? 33 : 65) : fp4 ? (down ? 7 : 4) : 17);
+    return T >= (bf16 ? (down ? 33 : 65) : fp4 ? (down ? 7 : kSkinnyMinTokens) : 17);
 }
 // Group rows up to which a group goes to the skinny tiles (the fp8 x fp8 kernels have none).
 inline int skinny_rows_of(int T, int act_quant) {

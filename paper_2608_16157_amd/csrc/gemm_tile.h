@@ -1,4 +1,4 @@
-// LDS-DMA and pipeline helpers shared by the MFMA expert kernels (gemm.hip, skinny.hip); internal.
+// LDS-DMA and pipeline helpers shared by the MFMA expert kernels (gemm.hip, skinny_tile.h); internal.
 #pragma once
 
 #include <type_traits>

@@ -202,8 +202,8 @@ __device__ void scan_experts(int E, int T, int k, int shared_slot, int skinny_ro
             wv.grp_len[g] = s_tot[e];
         }
     }
-    // the list tails and the shared expert's rows are written by route_scatter, spread over its
-    // workgroups
+    // the list tails and the shared expert's rows are written by every workgroup of route_scatter or
+    // route_place for its own tokens
 }
 
 // ---------------------------------------------------------------------------------------
@@ -695,7 +695,10 @@ __global__ __launch_bounds__(64) void route_scatter(RouteArgs a) {
 // 19.4 (of which route_tokens with a wave per token 3.5 to 4.5); 4096 tokens, layer: Qwen3 457 -> 450 us,
 // DeepSeek-V3 2454 -> 2391, DeepSeek-V4-Flash 862 -> 853 (routing 34 -> 20, 46 -> 33, 40 -> 25).  The
 // blocks' reads of the table grow with the square of the tokens: at 8192 tokens (512 blocks) the gain is
-// gone already with 128 experts (Qwen3 layer 755 us either way).
+// gone already with 128 experts (Qwen3 layer 755 us either way).  They grow with the experts too: at 4096
+// tokens, routing alone, four launches against two: 512 experts top 1 28.4 -> 24.1 us, top 8 37.1 -> 28.1;
+// 768: 32.5 -> 32.4, 44.2 -> 37.3; 1024: 39.1 -> 40.4, 50.3 -> 46.0 (3072 tokens 38.6 -> 35.7, 49.1 ->
+// 40.3).  So up to 256 blocks it is the better one for all but the fewest picks of 1024 experts.
 __global__ __launch_bounds__(1024) void route_place(RouteArgs a) {
     extern __shared__ int32_t lds[];
     const int E = a.E, k = a.k, T = a.T, nblk = gridDim.x, blk = blockIdx.x, tid = threadIdx.x;

@@ -156,6 +156,7 @@ __device__ __forceinline__ int slot_check(int raw, int e, int E, int n_slots, in
 constexpr int kWaveRouteMaxTokens = FT_ROUTE_WAVE_MAX_TOKENS;   // 0 disables the variant
 constexpr int kWaveRouteMaxNpl = 8;
 static_assert(kWaveRouteMaxTokens <= 2, "route_wave selects one batch of at most two tokens");
+static_assert(kWaveRouteMaxTokens < kSkinnyMinTokens, "skinny tiles read a group order that route_wave does not write");
 
 // LDS hand-off between the lanes of the one wave that routes: its own LDS operations complete in
 // order, so waiting for them is enough (no workgroup barrier, which would also count the other
