@@ -102,6 +102,17 @@ def algorithmic_work(lay, route, act_quant=0):
                 gateup_flops=rows * 4 * H * I, u_hit=u_hit, n_hit=n_hit, rows=rows)
 
 
+def few_row_tiles(T, H, I, w_dtype, down=False) -> bool:
+    """Whether a streaming call (T < 256) runs the few-row tiles rather than a GEMV in a projection: the
+    library's skinny_path, which a test compares with this copy."""
+    if w_dtype == 0 or T >= 256 or H > 8192 or I > 8192:
+        return False
+    k = I if down else H
+    if {1: 2 * k, 2: k, 3: k // 2}[w_dtype] % 4096 == 0 and not (w_dtype == 1 and down):
+        return T >= 96
+    return T >= {1: 33 if down else 65, 2: 17, 3: 7 if down else 4}[w_dtype]
+
+
 def kernel_source_sha(kernel: str) -> str:
     """Hash of the sources a dominant kernel is built from (its traffic figures are tied to it):
     the GEMM's or the GEMV's files plus the shared device and interface headers, and for the GEMM
@@ -662,8 +673,7 @@ def measure_forward(config, T, n_layers, steps, warmup, hip, combine=0, act_quan
                 "bytes_per_launch": round(gu_bytes), "ms_per_launch": round(gu_ms, 5)}
     else:
         achieved = gu_bytes / (gu_ms / 1e3) / 1e9
-        # the library's rule for the few-row tiles (skinny_path)
-        tiles = T >= {0: 256, 1: 65, 2: 17, 3: 4}[cfg.w_dtype]
+        tiles = few_row_tiles(T, cfg.hidden, cfg.inter, cfg.w_dtype)
         roof = {"kernel": "grouped gate/up few-row tiles + SiLU-mul (skinny_gemm<gate/up>)" if tiles else
                           "grouped gate/up GEMV + SiLU-mul (grouped_gemv<gate/up>)", "bound": "hbm",
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
