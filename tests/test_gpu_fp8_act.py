@@ -76,10 +76,10 @@ def oracle_aq(lay, tokens=None):
 
 CASES = [
     # seed, gating, E, k, T, n_res, shared, H, I, zipf
-    (0, 1, 32, 8, 1, 9, True, 384, 256, 0.0),       # streaming, one token
-    (1, 0, 12, 3, 20, 12, False, 256, 384, 0.0),    # streaming, narrow items
-    (2, 1, 8, 4, 60, 8, True, 256, 256, 0.0),       # streaming, wide gate/up items
-    (3, 0, 16, 4, 130, 10, True, 512, 384, 0.5),    # streaming, several M tiles a pass
+    (0, 1, 32, 8, 1, 9, True, 384, 256, 0.0),       # GEMV, one token
+    (1, 0, 12, 3, 20, 12, False, 256, 384, 0.0),    # few-row tiles, 3 K blocks in the down projection
+    (2, 1, 8, 4, 60, 8, True, 256, 256, 0.0),       # few-row tiles of more than 16 rows
+    (3, 0, 16, 4, 130, 10, True, 512, 384, 0.5),    # few-row tiles, groups of more than one
     (4, 1, 24, 6, 300, 10, True, 256, 256, 1.0),    # matrix cores, ragged groups
     (5, 0, 32, 8, 520, 13, True, 512, 384, 2.0),    # matrix cores, skewed
     (6, 1, 16, 4, 2900, 12, True, 256, 256, 3.0),   # matrix cores, groups over 1024 rows
@@ -102,7 +102,7 @@ def test_fp8_act_random_shapes(case):
         assert not out.any()
 
 
-@pytest.mark.parametrize("T", [20, 300])
+@pytest.mark.parametrize("T", [12, 20, 300])   # GEMVs, few-row tiles, matrix-core tiles
 def test_fp8_act_zero_block_scales(T):
     lay = workloads.random_layer(150 + T, hidden=512, inter=384, n_experts=8, top_k=3, tokens=T,
                                  w_dtype=workloads.DT_FP8, gating=1, n_resident=8, shared=True,

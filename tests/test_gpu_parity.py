@@ -280,17 +280,16 @@ RANDOM_FWD = [
     (18, workloads.DT_MXFP4, 0, 24, 6, 300, 14, True, 384, 256, 1.2),
     (19, workloads.DT_MXFP4, 1, 12, 3, 70, 0, True, 256, 256, 0.0),
     (20, workloads.DT_MXFP4, 0, 32, 8, 520, 13, False, 512, 384, 2.0),
-    # every streaming-kernel variant the launcher picks: T <= 16 takes the one-M-tile kernels;
-    # fp8 items are wide above 128 pairs, MXFP4 items above 12; the wide gate/up items take four M
-    # tiles a pass above 32 tokens (fp8) or from 64 (MXFP4); fp8 down items are wide, two K blocks
-    # a batch, above 32 tokens
-    (21, workloads.DT_FP8, 1, 32, 12, 16, 20, True, 256, 256, 0.0),    # fp8, one tile, wide
-    (22, workloads.DT_FP8, 0, 16, 4, 20, 10, False, 256, 384, 0.0),    # fp8, two tiles, narrow
-    (23, workloads.DT_MXFP4, 1, 16, 4, 16, 12, True, 256, 256, 0.0),   # MXFP4, one tile, wide
-    (24, workloads.DT_BF16, 0, 16, 4, 16, 16, True, 384, 256, 0.0),    # bf16, T = 16 exactly
-    (25, workloads.DT_FP8, 1, 8, 4, 60, 8, True, 256, 256, 0.0),       # fp8 wide gate/up, 4 M tiles a pass
-    (26, workloads.DT_MXFP4, 0, 16, 4, 100, 12, True, 256, 256, 0.7),  # MXFP4 wide gate/up, 4 M tiles a pass
-    (30, workloads.DT_FP8, 0, 16, 4, 48, 10, True, 512, 640, 0.5),     # fp8 wide down, 5 K blocks (tail batch)
+    # the edges of the streaming path: the one-M-tile GEMVs of up to 16 tokens with wide items (fp8
+    # above 128 pairs), and few-row tiles from 17 (fp8), 4 (MXFP4) tokens (the other GEMV variants:
+    # tests/test_gpu_gemv.py)
+    (21, workloads.DT_FP8, 1, 32, 12, 16, 20, True, 256, 256, 0.0),    # fp8 GEMV, one tile, wide
+    (22, workloads.DT_FP8, 0, 16, 4, 20, 10, False, 256, 384, 0.0),    # fp8 tiles
+    (23, workloads.DT_MXFP4, 1, 16, 4, 16, 12, True, 256, 256, 0.0),   # MXFP4 tiles of at most 16 rows
+    (24, workloads.DT_BF16, 0, 16, 4, 16, 16, True, 384, 256, 0.0),    # bf16 GEMV, T = 16 exactly
+    (25, workloads.DT_FP8, 1, 8, 4, 60, 8, True, 256, 256, 0.0),       # fp8 tiles of more than 16 rows
+    (26, workloads.DT_MXFP4, 0, 16, 4, 100, 12, True, 256, 256, 0.7),  # MXFP4 groups of more than one tile
+    (30, workloads.DT_FP8, 0, 16, 4, 48, 10, True, 512, 640, 0.5),     # fp8 tiles, 5 K blocks
     # groups above 1024 rows (more than one band of 8 M tiles, the last band short): strong skew
     # puts most tokens on the top experts, and the shared expert's 2900 rows make 23 M tiles
     (27, workloads.DT_BF16, 0, 16, 4, 2900, 12, True, 256, 256, 3.0),
@@ -370,10 +369,10 @@ def test_gemm_tile_classes(wdt):
     check_output(out, ref, wdt)
 
 
-@pytest.mark.parametrize("T", [20, 300])
+@pytest.mark.parametrize("T", [12, 20, 300])
 def test_fp8_zero_block_scales(T):
-    """fp8 block scales of 0 (the weights of that block are 0) on the streaming path (T = 20) and
-    the matrix-core path (T = 300): a zero first block, a run of zero blocks, a zero last block,
+    """fp8 block scales of 0 (the weights of that block are 0) in the GEMVs (T = 12), the few-row tiles
+    (T = 20) and the matrix-core tiles (T = 300): a zero first block, a run of zero blocks, a zero last block,
     and one expert whose gate/up scales are all zero."""
     lay = workloads.random_layer(50 + T, hidden=512, inter=384, n_experts=8, top_k=3, tokens=T,
                                  w_dtype=workloads.DT_FP8, gating=1, n_resident=8, shared=True,

@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (256, 6, 2048, False, False),   # 32 rows of the table per scanning thread
     (256, 6, 2049, True, False),    # a second batch of rows
     (256, 6, 4096, False, False),   # 256 blocks
+    (1024, 2, 4096, True, False),   # all 256 rows by one thread per expert
+    (8, 2, 4095, False, True),      # 128 scanning threads per expert
     (128, 8, 4097, True, False),    # one block too many
 ])
 def test_route_place(E, k, T, shared, ties):
