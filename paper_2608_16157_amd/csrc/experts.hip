@@ -4,7 +4,8 @@
 //
 // Streaming (GEMV-like) path, any token count and any weight dtype (larger decode batches run the
 // few-row tiles of gemm.hip in place of one or both projections, which form the same sums: skinny_path;
-// the wide items and the four M tiles per pass remain for H or I above those tiles' 8192):
+// the wide items and the four M tiles per pass remain for H or I above those tiles' 8192 and for weight
+// rows a multiple of 4096 bytes apart):
 //   grouped_gemv<GATEUP>: h[r] = silu(W1 x_tok(r)) * (W3 x_tok(r))       per (group, 8 NB h columns)
 //   grouped_gemv<DOWN>  : y[pair(r)] = gate(r) * W2 h[r]                 per (group, 16 NB columns)
 //   combine             : out[t] = sum_j y[t k + j] over the pairs evaluated on the GPU, in

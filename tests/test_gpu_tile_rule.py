@@ -17,8 +17,8 @@ BF16, FP8, MXFP4 = workloads.DT_BF16, workloads.DT_FP8, workloads.DT_MXFP4
 TOL = {BF16: 1e-2, FP8: 3e-2, MXFP4: 1e-2}
 
 
-def forward(lay, T, act_quant):
-    desc = dict(lay.desc(), act_quant=act_quant)
+def forward(lay, T, act_quant, combine=ftm.FT_COMBINE_ORDERED):
+    desc = dict(lay.desc(), act_quant=act_quant, combine=combine)
     ws, route = ftm.alloc_workspace(desc, T), ftm.RouteBuffers(T, lay.top_k, lay.n_experts)
     out = torch.full((T, lay.hidden), float("nan"), device="cuda")
     ftm.ft_moe_forward(desc, ftm.banks_of(lay), lay.logits[:T].contiguous(), lay.slot_table, lay.x[:T].contiguous(), T,
@@ -67,3 +67,21 @@ def test_same_bits_on_both_sides(wdt, few, many, H, I, changes):
     ref, _ = oracle.moe_partial(*oracle_inputs(lay), tokens=list(range(0, many, 7)))
     got = forward(lay, many, ftm.FT_ACT_EXACT)[::7].cpu().numpy()
     assert oracle.max_rel_err(got, ref[::7]) <= TOL[wdt]
+
+
+@pytest.mark.parametrize("wdt,T,H,I,ran", [
+    (BF16, 40, 256, 128, (False, True)),
+    (MXFP4, 5, 256, 128, (True, False)),
+    (FP8, 40, 128, 4096, (True, False)),
+])
+def test_atomic_combine_of_mixed_kernels(wdt, T, H, I, ran):
+    """A GEMV in one projection and tiles in the other: whichever runs first zeroes the output that the other
+    adds into."""
+    assert kernels(T, H, I, wdt) == ran
+    lay = workloads.random_layer(T, hidden=H, inter=I, n_experts=6, top_k=3, tokens=T, w_dtype=wdt, n_resident=5,
+                                 shared=True, device="cuda")
+    ref, _ = oracle.moe_partial(*oracle_inputs(lay))
+    for act in (ftm.FT_ACT_EXACT, ftm.FT_ACT_FP8_1x128_POW2) if wdt == FP8 else (ftm.FT_ACT_EXACT,):
+        got = forward(lay, T, act, ftm.FT_COMBINE_ATOMIC)
+        torch.testing.assert_close(got, forward(lay, T, act), rtol=1e-5, atol=1e-5 * float(got.abs().max()))
+    assert oracle.max_rel_err(forward(lay, T, ftm.FT_ACT_EXACT, ftm.FT_COMBINE_ATOMIC).cpu().numpy(), ref) <= TOL[wdt]
