@@ -692,10 +692,10 @@ __global__ __launch_bounds__(64) void route_scatter(RouteArgs a) {
 // offsets, counts and groups.  A scan in a workgroup of its own costs launches and several dependent
 // rounds of global memory more: routing stage (with its events) at Qwen3 777 tokens 25.8 -> 15.5 us,
 // DeepSeek-V3 300 tokens 31.3 -> 18.6, 2048 tokens 33.3 -> 19.3, DeepSeek-V4-Flash 1500 tokens 31.8 ->
-// 19.4 (of which route_tokens with a wave per token 3.5 to 4.5); 4096 tokens, layer: Qwen3 457 -> 450 us,
-// DeepSeek-V3 2454 -> 2391, DeepSeek-V4-Flash 862 -> 853 (routing 34 -> 20, 46 -> 33, 40 -> 25).  The
-// blocks' reads of the table grow with the square of the tokens: at 8192 tokens (512 blocks) the gain is
-// gone already with 128 experts (Qwen3 layer 755 us either way).  They grow with the experts too: at 4096
+// 19.4 (of which route_tokens with a wave per token 3.5 to 4.5); 4096 tokens: Qwen3 34 -> 20, DeepSeek-V3
+// 46 -> 33, DeepSeek-V4-Flash 40 -> 25.  The blocks' reads of the table grow with the square of the tokens:
+// at 8192 tokens (512 blocks) the gain is gone already with 128 experts (Qwen3 layer 755 us either way).
+// They grow with the experts too: at 4096
 // tokens, routing alone, four launches against two: 512 experts top 1 28.4 -> 24.1 us, top 8 37.1 -> 28.1;
 // 768: 32.5 -> 32.4, 44.2 -> 37.3; 1024: 39.1 -> 40.4, 50.3 -> 46.0 (3072 tokens 38.6 -> 35.7, 49.1 ->
 // 40.3).  So up to 256 blocks it is the better one for all but the fewest picks of 1024 experts.
