@@ -202,11 +202,11 @@ __device__ __forceinline__ void mfma_kblock(const u32x4_t (&av)[ALd<WT>::n], con
 // up to MTX M tiles per pass (MTX = 1 when no group can hold more than 16 rows, which keeps the
 // register count, and so the occupancy, of few-token calls down).  Each activation load feeds
 // the NB weight blocks of the item.
-// Workgroups per CU the bf16 kernels are held to (128 registers a lane, no spills): one more
-// than the register count the compiler picks by itself allows; two for the gate/up kernels whose
-// deeper batches fill that much LDS.  The narrow fp8 kernels of one M tile need 128 registers to within
-// four; the other fp8 kernels and the MXFP4 ones would spill under the same bound and keep the compiler's
-// choice.
+// Workgroups per CU the bf16 kernels are held to (128 registers a lane; of them only the four-way split
+// down kernel of several M tiles spills, 28 bytes a lane): one more than the register count the compiler
+// picks by itself allows; two for the gate/up kernels whose deeper batches fill that much LDS.  The narrow
+// fp8 kernels of one M tile need 128 registers to within four; the other fp8 kernels and the MXFP4 ones
+// would spill under the same bound and keep the compiler's choice.
 template <int WT, int EPI, int NB, int MTX> constexpr int gemv_min_blocks() {
     if (WT == FT_DT_FP8E4M3FN_B128 && NB == 2 && MTX == 1) return 4;
     return WT != FT_DT_BF16 ? 1 : (EPI == EPI_GATEUP && MTX > 1 && FT_GEMV_DGU_BF16 > 1 ? 2 : 4);
